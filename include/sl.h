@@ -86,8 +86,8 @@ typedef struct sl_attn_desc {
     int32_t max_blocks_per_seq; /* row length of block_table */
     int32_t num_pages;          /* pages in each pool; valid page ids are [0, num_pages) */
     int32_t num_workers;        /* split-KV workers (wavefronts). 0: library default
-                                   (three per CU for bf16, four per CU for FP8 and for
-                                   prefix-shared attention); 1..65536: exactly this
+                                   (three per CU for bf16 with head_dim 128, else four
+                                   per CU); 1..65536: exactly this
                                    many. The result does not depend on it beyond fp32
                                    rounding; tests vary it to exercise the merge. */
     hipStream_t stream;         /* stream the work is enqueued on (0: null stream) */

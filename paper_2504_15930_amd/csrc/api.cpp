@@ -116,7 +116,7 @@ sl_status check_desc(const sl_attn_desc *d)
     if ((long long)d->batch * d->max_blocks_per_seq * d->num_kv_heads >= (1LL << 28) ||
         (long long)d->max_blocks_per_seq * kPageSize >= (1LL << 31) ||
         (long long)d->num_pages * d->num_kv_heads >= (1LL << 31) ||
-        (long long)d->batch * d->num_q_heads >= (1LL << (32 - kMetaRowShift)))
+        (long long)d->batch * d->num_q_heads >= (1LL << (32 - kMetaUnitShift)))
         return SL_ERR_UNSUPPORTED;
     if (d->num_workers > kMaxWorkers)
         return SL_ERR_UNSUPPORTED;
@@ -137,11 +137,14 @@ sl_status resolve_workers(const sl_attn_desc *d, bool fp8, int *nw, bool prefix 
     // whose tiles carry twice the bytes, already saturates HBM with three
     // workgroups per four CUs (1.5-2.5% faster than one per CU, as fewer
     // streams compete for the memory; 640 or fewer workers, or 1280 and more,
-    // were slower). Two waves per SIMD were slower for both. Prefix-shared
-    // attention keeps one own-page workgroup per CU beside its shared-page
+    // were slower). With head_dim 64 a bf16 tile carries half the bytes, and
+    // one per CU is as fast or faster (132 against 130 us on 384 sequences of
+    // 1..2048 tokens; one tile per step: 150 against 132). Two waves per SIMD
+    // were slower for all but E4M3 with head_dim 64 and one tile per step.
+    // Prefix-shared attention keeps one own-page workgroup per CU beside its shared-page
     // workgroups (three per four CUs was 12% slower).
     const int blocks = info->blocks[d->head_dim == 128][fp8 ? 1 : 0];
-    const int per_cu4 = fp8 || prefix ? 4 : 3;   // workgroups per four CUs
+    const int per_cu4 = fp8 || prefix || d->head_dim == 64 ? 4 : 3;   // workgroups per four CUs
     *nw = (blocks > 0 ? info->cus * per_cu4 / 4 : info->cus) * kWavesPerBlock;
     if (*nw > kMaxWorkers)
         *nw = kMaxWorkers;
@@ -231,6 +234,7 @@ sl_status run(const sl_attn_desc *d, const uint16_t *q, const void *k_pages, con
     mp.num_kv_heads = d->num_kv_heads;
     mp.group = G;
     mp.num_workers = nw;
+    mp.step_tiles = split_step_tiles(d->head_dim, fp8);
     mp.next_kind = 0;
     if (next) {
         mp.next = *next;
@@ -404,6 +408,7 @@ sl_status run_prefix(const sl_attn_desc *d, const uint16_t *q, const void *k_pag
     mp.num_shared_workers = nws;
     mp.max_shared_workers = nws_max;
     mp.max_blocks = d->max_blocks_per_seq;
+    mp.step_tiles = split_step_tiles(d->head_dim, fp8);
     if (launch_merge_prefix(mp, d->head_dim, d->stream) != hipSuccess)
         return SL_ERR_HIP;
     return SL_OK;

@@ -171,9 +171,12 @@ __device__ __forceinline__ void append_row(const AppendParams &p, int unit, int 
     if constexpr (!FP8) {
         uint16_t *kd = static_cast<uint16_t *>(p.k_pages) + (tile * kPageSize + slot) * D;
         uint16_t *vd = static_cast<uint16_t *>(p.v_pages) + (tile * kPageSize + slot) * D;
-        for (int i = lane; i < D / 2; i += kWave) {
-            reinterpret_cast<uint32_t *>(kd)[i] = reinterpret_cast<const uint32_t *>(kx)[i];
-            reinterpret_cast<uint32_t *>(vd)[i] = reinterpret_cast<const uint32_t *>(vx)[i];
+        static_assert(D / 2 <= kWave, "one dword of each row per lane");
+        if (lane < D / 2) {   // both loads first: a store between them would wait for the first
+            const uint32_t kw = reinterpret_cast<const uint32_t *>(kx)[lane];
+            const uint32_t vw = reinterpret_cast<const uint32_t *>(vx)[lane];
+            reinterpret_cast<uint32_t *>(kd)[lane] = kw;
+            reinterpret_cast<uint32_t *>(vd)[lane] = vw;
         }
     } else {
         uint8_t *kt = static_cast<uint8_t *>(p.k_pages) + tile * kPageSize * D;
@@ -191,11 +194,15 @@ template <int D, bool FP8>
 __device__ __forceinline__ void append_unit(const AppendParams &p, int unit, int lane)
 {
     const int b = unit / p.num_kv_heads;
-    const int L = p.stage ? p.stage[b] : p.seq_lens[b];
+    if (p.stage) {   // both across the host link: fetched together
+        const int L = p.stage[b], page = p.stage[p.batch + b];
+        append_row<D, FP8>(p, unit, L, page, lane);
+        return;
+    }
+    const int L = p.seq_lens[b];
     if (L <= 0 || L > p.max_blocks * kPageSize)
         return;
-    const int page = p.stage ? p.stage[p.batch + b] : p.block_table[(size_t)b * p.max_blocks + (L - 1) / kPageSize];
-    append_row<D, FP8>(p, unit, L, page, lane);
+    append_row<D, FP8>(p, unit, L, p.block_table[(size_t)b * p.max_blocks + (L - 1) / kPageSize], lane);
 }
 
 }  // namespace

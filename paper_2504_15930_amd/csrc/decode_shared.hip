@@ -46,17 +46,21 @@ namespace {
 // reads the shared pages once: the shared stream has one "sequence" per
 // sub-group. Builds in LDS, with every pass parallel over groups,
 // sub-groups or sequences:
-//   s_group[b]  the sub-group of sequence b (-1: none; B + 1 entries, the
-//               last one scratch),
+//   s_shared[b] the shared pages of sequence b (B + 1 entries, the last one
+//               scratch),
 //   s_len[b]    the lengths,
-//   s_own[0..B] the exclusive prefix sum of own (unshared) pages per sequence,
-//   s_sh[0..S]  the exclusive prefix sum of shared pages per sub-group, and
-//   s_gl[s]     each sub-group's first member and size, lead | (members - 1) << 16,
+//   s_own[0..B] the exclusive prefix sum of steps (of NT pages) over the own
+//               (unshared) pages per sequence,
+//   s_sh[0..S]  the exclusive prefix sum of steps over the shared pages per
+//               sub-group, and
+//   s_gl[s]     each sub-group's first member, size and the pages missing from
+//               its last step, lead | (members - 1) << 16 | missing << 24,
 // where S = max_sub bounds the sub-group count (sub-groups past the real
 // count have no pages). Workgroup 0 also stores the sums and every
 // sequence's sharing descriptor for the merge.
+template <int NT>
 __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const PrefixParams &pp, int32_t *s_own,
-                                                   int32_t *s_len, int32_t *s_group, int32_t *s_sh, int32_t *s_gl,
+                                                   int32_t *s_len, int32_t *s_shared, int32_t *s_sh, int32_t *s_gl,
                                                    int32_t *s_gs, int32_t *s_sp)
 {
     constexpr int T = kWave * kWavesPerBlock;
@@ -69,6 +73,7 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
     // NG == B) and s_own (B + 1 entries).
     int32_t *const s_prev_end = s_len;   // [NG + 1]: largest end of the earlier groups
     int32_t *const s_base = s_own;       // [NG + 1]: first sub-group of each group
+    int32_t *const s_group = s_shared;   // [B + 1]: marks of the groups' first members
     // 1. Each group's earlier ends; every sequence starts unmarked. With
     //    group_start ascending (the usual case) the largest earlier end of
     //    group k is its own start, and the scan is skipped.
@@ -121,7 +126,7 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
             const int ns = (m + M - 1) / M, cm = (m + ns - 1) / ns;
             const int slo = lo + (sg - s_base[klo]) * cm;
             sp = s_sp[klo];
-            gl = slo | (min(cm, lo + m - slo) - 1) << 16;
+            gl = slo | (min(cm, lo + m - slo) - 1) << 16 | (NT - 1 - (sp + NT - 1) % NT) << 24;
         }
         s_sh[sg] = sp;
         s_gl[sg] = gl;
@@ -146,23 +151,24 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
         }
     }
     __syncthreads();
+    // 5. Lengths, shared pages and own steps (over the pages after the
+    //    sub-group's shared ones).
+    const int max_len = p.max_blocks * kPageSize;
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
         const int b = tid + r * T;
-        if (b < B)
-            s_group[b] = sub[r];
+        if (b < B) {
+            const int L = p.seq_lens[b];
+            const int n = pages_of(L, max_len);
+            const int sh = sub[r] >= 0 ? s_sh[sub[r]] : 0;
+            s_len[b] = L;
+            s_shared[b] = sh;
+            s_own[b] = n > sh ? (n - sh + NT - 1) / NT : 0;
+        }
     }
     __syncthreads();
-    // 5. Lengths and own pages (the pages after the sub-group's shared ones).
-    const int max_len = p.max_blocks * kPageSize;
-    for (int b = tid; b < B; b += T) {
-        const int L = p.seq_lens[b];
-        const int k = s_group[b];
-        const int n = pages_of(L, max_len);
-        const int sh = k >= 0 ? s_sh[k] : 0;
-        s_len[b] = L;
-        s_own[b] = n > sh ? n - sh : 0;
-    }
+    for (int sg = tid; sg < S; sg += T)
+        s_sh[sg] = (s_sh[sg] + NT - 1) / NT;
     __syncthreads();
     block_exclusive_scan2<ScanSum, ScanSum>(s_own, B, s_sh, S);
     if (blockIdx.x == 0) {
@@ -171,10 +177,13 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
         for (int i = tid; i <= S; i += T)
             pp.cum_shared[i] = s_sh[i];
         typedef int32_t i32x4_t __attribute__((ext_vector_type(4)));
-        for (int i = tid; i < B; i += T) {
-            const int k = s_group[i];
-            *reinterpret_cast<i32x4_t *>(pp.seq_shared + 4 * (size_t)i) =
-                k >= 0 ? i32x4_t{s_sh[k], s_sh[k + 1] - s_sh[k], s_gl[k] & 0xffff, k} : i32x4_t{0, 0, 0, -1};
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            const int b = tid + r * T, k = sub[r];
+            if (b < B)
+                *reinterpret_cast<i32x4_t *>(pp.seq_shared + 4 * (size_t)b) =
+                    k >= 0 ? i32x4_t{s_sh[k], s_shared[b], s_gl[k] & 0xffff, s_sh[k + 1] - s_sh[k]}
+                           : i32x4_t{0, 0, 0, 0};
         }
     }
 }
@@ -192,23 +201,24 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void prefix_split_kernel(Sp
     extern __shared__ int32_t s_dyn[];
     const int B = own.batch, S = pp.max_sub;
     int32_t *const s_own = s_dyn;             // [B + 1]
-    int32_t *const s_group = s_own + B + 1;   // [B + 1]
-    int32_t *const s_len = s_group + B + 1;   // [B]
+    int32_t *const s_shared = s_own + B + 1;  // [B + 1]
+    int32_t *const s_len = s_shared + B + 1;  // [B]
     int32_t *const s_sh = s_len + B;          // [S + 1]
     int32_t *const s_gl = s_sh + S + 1;       // [S]
     int32_t *const s_gs = s_gl + S;           // [NG + 1]
     int32_t *const s_sp = s_gs + pp.num_groups + 1;   // [NG]
-    scan_prefix_groups(own, pp, s_own, s_len, s_group, s_sh, s_gl, s_gs, s_sp);
+    constexpr int NT = step_tiles<D, FP8>();
+    scan_prefix_groups<NT>(own, pp, s_own, s_len, s_shared, s_sh, s_gl, s_gs, s_sp);
     if ((int)blockIdx.x < own_blocks)
         split_unit_worker<D, FP8, kOwnPages>(
             own, blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
-            StreamLds{s_own, s_len, s_group, s_sh});
+            StreamLds{s_own, s_len, s_shared});
     else {
         SplitParams sh = shared;
         sh.num_workers = effective_shared_workers((long long)s_own[B] * own.num_kv_heads, own.num_workers,
-                                                  shared.num_workers, max_shared);
+                                                  shared.num_workers, max_shared, NT);
         split_unit_worker<D, FP8, kSharedPages>(sh, (int)blockIdx.x - own_blocks,
-                                                  StreamLds{s_sh, nullptr, nullptr, nullptr, s_gl, S},
+                                                  StreamLds{s_sh, nullptr, nullptr, s_gl, S},
                                                   __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
     }
 }

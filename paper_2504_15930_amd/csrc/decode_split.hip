@@ -21,10 +21,10 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void split_kv_kernel(SplitP
     extern __shared__ int32_t s_dyn[];
     int32_t *const s_cum = s_dyn;                // [B + 1]
     int32_t *const s_len = s_dyn + p.batch + 1;  // [B]
-    scan_sequences(p, s_cum, s_len);
+    scan_sequences<step_tiles<D, FP8>()>(p, s_cum, s_len);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     split_unit_worker<D, FP8, kAllPages>(p, wave * (int)gridDim.x + (int)blockIdx.x,
-                                         StreamLds{s_cum, s_len, nullptr, nullptr});
+                                         StreamLds{s_cum, s_len});
 }
 
 }  // namespace
@@ -59,6 +59,12 @@ hipError_t split_blocks_per_cu(int head_dim, bool fp8, int *blocks)
     if (head_dim == 64 && fp8)
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, split_kv_kernel<64, true>, threads, 0);
     return hipErrorInvalidValue;
+}
+
+int split_step_tiles(int head_dim, bool fp8)
+{
+    return head_dim == 64 ? (fp8 ? step_tiles<64, true>() : step_tiles<64, false>())
+                          : (fp8 ? step_tiles<128, true>() : step_tiles<128, false>());
 }
 
 }  // namespace sl

@@ -30,11 +30,12 @@
 // line per instruction (each row spread over four lanes), which streams at
 // ~6.0 TB/s instead of ~6.85 TB/s on MI355X, so K is read in whole 1 KB runs
 // and regrouped through a small per-wave LDS buffer. Both are streamed with
-// non-temporal loads. Tiles are software-pipelined (pipeline_depth);
-// the block-table entry of a tile (its unit metadata comes from a cursor over
-// the units) is fetched one pipeline turn before the tile itself, and the
-// query rows of a unit are loaded together with the unit's first tile, so the
-// stream never waits on a dependent load, also across unit boundaries.
+// non-temporal loads. A worker goes through its range in steps of one, two or
+// four tiles (step_tiles), software-pipelined; the steps' units, pages and
+// block-table entries are worked out 64 at a time, one per lane, ahead of the
+// steps themselves, and the query rows of a unit are loaded together with the
+// unit's first step, so the stream never waits on a dependent load, also
+// across unit boundaries.
 //
 // FP8 pages hold OCP E4M3 codes; they are widened to bf16 exactly
 // (v_cvt_scalef32_pk_bf16_fp8 with unit scale), the per-(page, head) key
@@ -59,30 +60,25 @@ constexpr float kNegInf = -__builtin_inff();
 // more than this slack (base-2 units), which bounds the weights by 2^8 and
 // leaves the accumulators untouched on most tiles after a unit's first.
 constexpr float kRescaleSlack = 8.0f;
-// Tiles in the software pipeline: two for a bf16 cache (three and four
-// measured the same); three for E4M3, whose tiles carry half the bytes for
-// the same work per tile.
-template <bool FP8>
-constexpr int pipeline_depth() { return FP8 ? 3 : 2; }
+// Tiles per pipeline step and steps in flight. A worker is one wavefront, most
+// often alone on its SIMD, so its chain of dependent instructions per tile is
+// time that nothing fills: at 1024 workers a wavefront has ~0.65 us for an
+// E4M3 tile of 4 KB before HBM waits for it. Two tiles per step share the
+// bookkeeping, the look at the running maximum and half of the value MFMAs
+// (compute_step); a step then carries as many bytes as one bf16 tile of D =
+// 128, which is HBM-bound with one tile per step (two measured the same to 1%
+// slower). Step (split + merge) with one tile -> this choice, MI355X:
+//   bf16 D = 64, 384 x 1..2048 tokens, 8 KV heads   165 -> 130 us (with 1024 workers)
+//   E4M3 D = 128, 512 x 512 + lognormal(2048)        319 -> 316 us; at 768 workers 381 -> 327
+//   E4M3 D = 64, 384 x 1..4096 tokens, 8 KV heads   226 -> 146 us (two tiles: 157)
+// Two steps in flight; three were no faster anywhere (and slower where they
+// cost a resident workgroup, in the prefix kernel).
+template <int D, bool FP8>
+constexpr int step_tiles() { return D == 64 ? (FP8 ? 4 : 2) : (FP8 ? 2 : 1); }
+constexpr int kPipelineDepth = 2;
 constexpr int kRawBufferWord3 = 0x00020000;  // untyped 32-bit buffer resource (CDNA3/4)
 
 __device__ __forceinline__ u32x4_t ld128(const uint8_t *p) { return *reinterpret_cast<const u32x4_t *>(p); }
-
-// K/V pages are read exactly once per call: stream them with non-temporal loads
-// so they do not displace reusable lines in L2 / the Infinity Cache (measured on
-// MI355X: random 4 KB tiles reach ~6.8 TB/s this way, ~6.0 TB/s with plain loads).
-__device__ __forceinline__ u32x4_t ld128_stream(const uint8_t *p)
-{
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
-}
-__device__ __forceinline__ u32x2_t ld64_stream(const uint8_t *p)
-{
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(p));
-}
-__device__ __forceinline__ uint32_t ld32_stream(const uint8_t *p)
-{
-    return __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p));
-}
 
 // Two fp32 -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
@@ -123,10 +119,16 @@ struct Tile {
     static constexpr int VW = FP8 ? D / 16 : D / 8;
     uint32_t k[KW];
     uint32_t v[VW];
-    u32x4_t q[D / 32];   // the unit's query rows, loaded with a unit's first tile only
     float scl;           // FP8: key scale in lanes 0-31, value scale in lanes 32-63
-    uint32_t meta;       // tile metadata (kMeta* bits, wave-uniform)
-    bool bad_page;       // the block table named a page outside the pool
+};
+
+// One pipeline step: NT consecutive tiles of one unit (fewer at the unit's end).
+template <int D, bool FP8, int NT>
+struct Step {
+    Tile<D, FP8> t[NT];
+    u32x4_t q[D / 32];   // the unit's query rows, loaded with a unit's first step only
+    uint32_t meta;       // metadata (kMeta* bits, wave-uniform)
+    int32_t valid;       // live tokens of the step, 1 .. 16 NT; kSharedPages: | (members - 1) << 8
 };
 
 // Query element index held by (quad, item) in k-step s; must match k_operand.
@@ -136,83 +138,123 @@ __device__ __forceinline__ int q_index(int s, int quad)
     return FP8 ? quad * (D / 4) + 8 * s : 32 * s + 8 * quad;
 }
 
-// Issue every load of one tile. All loads are unconditional. K/V are streamed
-// with non-temporal loads (STREAM) unless the tile is read by several
-// wavefronts at once (the column blocks of a shared unit), where plain loads
-// let the siblings find it in L2. `blk` < 0: a single-unit tile, whose query
-// rows are the group's G heads; `blk` >= 0: column block blk of a shared unit
-// (rows 16 blk + n, member r / G and head r % G of the group).
-template <int D, bool FP8, bool STREAM = true>
-__device__ __forceinline__ void issue_tile(Tile<D, FP8> &t, const SplitParams &p, int32_t page,
-                                           uint32_t meta, bool with_q, int n, int quad, int lane, int blk = -1)
+// K/V pages are read exactly once per call: stream them with non-temporal loads
+// so they do not displace reusable lines in L2 / the Infinity Cache (measured on
+// MI355X: random 4 KB tiles reach ~6.8 TB/s this way, ~6.0 TB/s with plain loads).
+constexpr int kCachePolicyStream = 2;   // NT
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, uint32_t bytes)
 {
-    auto ld128_kv = [](const uint8_t *a) { return STREAM ? ld128_stream(a) : ld128(a); };
-    auto ld64_kv = [](const uint8_t *a) {
-        return STREAM ? ld64_stream(a) : *reinterpret_cast<const u32x2_t *>(a);
-    };
-    auto ld32_kv = [](const uint8_t *a) {
-        return STREAM ? ld32_stream(a) : *reinterpret_cast<const uint32_t *>(a);
-    };
-    constexpr size_t kTileBytes = (size_t)kPageSize * D * (FP8 ? 1 : 2);
-    t.meta = meta;
-    t.bad_page = page < 0;
-    const size_t tile = (size_t)(page < 0 ? 0 : page);
-    const uint8_t *kt = static_cast<const uint8_t *>(p.k_pages) + tile * kTileBytes;
-    const uint8_t *vt = static_cast<const uint8_t *>(p.v_pages) + tile * kTileBytes;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, kRawBufferWord3);
+}
+
+// The score-MFMA B operands of a unit with first query row row0, zero where
+// `with_q` is false: lane (n, quad) takes query row n, and the rows past the
+// group's G lie past the resource's end, so they are zero too.
+template <int D, bool FP8>
+__device__ __forceinline__ void load_q(u32x4_t (&q)[D / 32], const SplitParams &p, uint32_t row0, bool with_q, int n,
+                                       int quad)
+{
+    const __amdgpu_buffer_rsrc_t qr = buffer_of(p.q + (size_t)row0 * D, with_q ? (uint32_t)(p.group * D * 2) : 0u);
+#pragma unroll
+    for (int s = 0; s < D / 32; ++s)
+        q[s] = __builtin_bit_cast(
+            u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(qr, 2 * (n * D + q_index<D, FP8>(s, quad)), 0, 0));
+}
+
+// Issue the K/V loads of one tile (page-head tile index `tile`), always the
+// same number of them: the compiler's counter waits can then tell the loads of
+// one step from those of the next. (A load issued on some paths only makes
+// every later wait assume the path with the fewest, and so drain loads that
+// should stay in flight.) What must not be read (`read` false: a tile past the
+// range, a page outside the pool) goes through a buffer resource of zero
+// bytes, whose loads return zeros without touching memory.
+//
+// K/V are streamed with non-temporal loads (STREAM) unless the tile is read by
+// several wavefronts at once (the column blocks of a shared unit), where plain
+// loads let the siblings find it in L2.
+template <int D, bool FP8, bool STREAM>
+__device__ __forceinline__ void issue_tile(Tile<D, FP8> &t, const SplitParams &p, uint32_t tile_index, bool read,
+                                           int n, int quad, int lane)
+{
+    constexpr int kPolicy = STREAM ? kCachePolicyStream : 0;
+    constexpr uint32_t kTileBytes = kPageSize * D * (FP8 ? 1 : 2);
+    const size_t tile = tile_index;
+    const __amdgpu_buffer_rsrc_t kt =
+        buffer_of(static_cast<const uint8_t *>(p.k_pages) + tile * kTileBytes, read ? kTileBytes : 0u);
+    const __amdgpu_buffer_rsrc_t vt =
+        buffer_of(static_cast<const uint8_t *>(p.v_pages) + tile * kTileBytes, read ? kTileBytes : 0u);
     // K: whole 1 KB runs per instruction (lane l reads bytes 16 l of each
     // run), so every instruction covers complete 128-byte lines; the rows are
     // regrouped into the score-MFMA layout through LDS when the tile is used.
 #pragma unroll
     for (int i = 0; i < Tile<D, FP8>::KW / 4; ++i) {
-        const u32x4_t x = ld128_kv(kt + 1024 * i + 16 * lane);
+        const u32x4_t x = __builtin_bit_cast(
+            u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(kt, 16 * lane + 1024 * i, 0, kPolicy));
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             t.k[4 * i + c] = x[c];
     }
-    if constexpr (!FP8) {
+    // V: lane (n, quad) reads D/16 consecutive elements of rows 4 quad + r.
+    constexpr int kRow = D * (FP8 ? 1 : 2);
+    const int voff = 4 * quad * kRow + n * (kRow / 16);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint8_t *src = vt + ((4 * quad + r) * D + n * (D / 16)) * 2;
-            if constexpr (D == 128) {
-                const u32x4_t x = ld128_kv(src);
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (kRow == 256) {
+            const u32x4_t x = __builtin_bit_cast(
+                u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(vt, voff + r * kRow, 0, kPolicy));
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    t.v[4 * r + c] = x[c];
-            } else {
-                const u32x2_t x = ld64_kv(src);
-                t.v[2 * r] = x[0];
-                t.v[2 * r + 1] = x[1];
-            }
+            for (int c = 0; c < 4; ++c)
+                t.v[4 * r + c] = x[c];
+        } else if constexpr (kRow == 128) {
+            const u32x2_t x =
+                __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(vt, voff + r * kRow, 0, kPolicy));
+            t.v[2 * r] = x[0];
+            t.v[2 * r + 1] = x[1];
+        } else {
+            t.v[r] = __builtin_bit_cast(uint32_t,
+                                        __builtin_amdgcn_raw_buffer_load_b32(vt, voff + r * kRow, 0, kPolicy));
         }
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint8_t *src = vt + (4 * quad + r) * D + n * (D / 16);
-            if constexpr (D == 128) {
-                const u32x2_t x = ld64_kv(src);
-                t.v[2 * r] = x[0];
-                t.v[2 * r + 1] = x[1];
-            } else {
-                t.v[r] = ld32_kv(src);
-            }
-        }
+    }
+    if constexpr (FP8) {
         const float *sp = (lane & 32) ? p.v_scales : p.k_scales;
         t.scl = sp[tile];
     }
-    // The query rows of a unit travel with the unit's first tile (or the
-    // worker's first tile); lanes past the group read row G - 1 and are zeroed
-    // when the operand is formed.
-    if (with_q) {
-        const int G = p.group;
-        int rel = min(n, G - 1);
-        if (blk >= 0) {   // rows past the shared unit's read its first row (never written out)
-            const int r = 16 * blk + n;
-            rel = r < ((int)(meta & 15u) + 1) * G ? (r / G) * p.num_q_heads + r % G : 0;
-        }
-        const uint16_t *qrow = p.q + ((size_t)(meta >> kMetaRowShift) + (size_t)rel) * D;
+}
+
+// Issue the loads of a step: tiles T[u] (a page-head tile index, or the
+// complement ~i of one for a tile that is not to be read: past the unit's end
+// or in a page outside the pool; its scales are those of tile i) and, `with_q`,
+// the unit's query rows. `live` false: a step past the range, nothing is read.
+// `blk` < 0: a single-unit step, whose query rows are the group's G heads;
+// `blk` >= 0: column block blk of a shared unit (rows 16 blk + n, member r / G
+// and head r % G of the group).
+template <int D, bool FP8, int NT, bool STREAM>
+__device__ __forceinline__ void issue_step(Step<D, FP8, NT> &st, const SplitParams &p, const int32_t (&T)[NT],
+                                           bool live, bool with_q, int n, int quad, int lane, int blk)
+{
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+        issue_tile<D, FP8, STREAM>(st.t[u], p, (uint32_t)(T[u] ^ (T[u] >> 31)), live && T[u] >= 0, n, quad, lane);
+    const uint32_t row0 = (st.meta >> kMetaUnitShift) * (uint32_t)p.group;
+    if (blk < 0) {
+        // One tile per step: the q loads are issued only where they read
+        // something. Without them in every step the HBM-bound bf16 stream of
+        // D = 128 is 0.2% faster; the waits then treat a unit's first step as
+        // if its q loads were not there and drain four more loads of the next
+        // step once per unit, which costs the others more (D = 64 bf16, 130
+        // against 137 us; E4M3 D = 128, 313 against 316).
+        if (NT > 1 || with_q)
+            load_q<D, FP8>(st.q, p, row0, with_q, n, quad);
+    } else {   // rows past the shared unit's read its first row (never written out)
+        const int r = 16 * blk + n, G = p.group;
+        const uint32_t rel = r < ((st.valid >> 8) + 1) * G ? (uint32_t)((r / G) * p.num_q_heads + r % G) : 0u;
+        const __amdgpu_buffer_rsrc_t qr = buffer_of(p.q + (size_t)row0 * D, with_q ? 0xffffffffu : 0u);
 #pragma unroll
         for (int s = 0; s < D / 32; ++s)
-            t.q[s] = ld128(reinterpret_cast<const uint8_t *>(qrow + q_index<D, FP8>(s, quad)));
+            st.q[s] = __builtin_bit_cast(
+                u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                             qr, (int)(2u * (rel * (uint32_t)D + (uint32_t)q_index<D, FP8>(s, quad))), 0, 0));
     }
 }
 
@@ -222,25 +264,31 @@ __device__ __forceinline__ void issue_tile(Tile<D, FP8> &t, const SplitParams &p
 // starting at quad D/64. A chunk c of row r is stored at position
 // c ^ ((r / P) % C) of its row (P rows per 256 bytes, C chunks per row), which
 // makes the 16-lane groups of both the writes and the reads hit distinct banks.
-template <int D, bool FP8>
-__device__ __forceinline__ void regroup_k(const Tile<D, FP8> &t, uint8_t *lds, int lane, int n, int quad,
-                                          u32x4_t (&kc)[FP8 ? D / 64 : D / 32])
+template <int D, bool FP8, int NT>
+__device__ __forceinline__ void regroup_k(const Tile<D, FP8> (&t)[NT], uint8_t *lds, int lane, int n, int quad,
+                                          u32x4_t (&kc)[NT][FP8 ? D / 64 : D / 32])
 {
     constexpr int R = D * (FP8 ? 1 : 2);   // bytes per row
     constexpr int C = R / 16;               // 16-byte chunks per row
     constexpr int P = 256 / R;              // rows per 256 bytes
 #pragma unroll
-    for (int i = 0; i < Tile<D, FP8>::KW / 4; ++i) {
-        const int off = 1024 * i + 16 * lane;
-        const int r = off / R, c = (off % R) / 16;
-        *reinterpret_cast<u32x4_t *>(lds + r * R + 16 * (c ^ ((r / P) % C))) =
-            u32x4_t{t.k[4 * i], t.k[4 * i + 1], t.k[4 * i + 2], t.k[4 * i + 3]};
+    for (int u = 0; u < NT; ++u) {
+#pragma unroll
+        for (int i = 0; i < Tile<D, FP8>::KW / 4; ++i) {
+            const int off = 1024 * i + 16 * lane;
+            const int r = off / R, c = (off % R) / 16;
+            *reinterpret_cast<u32x4_t *>(lds + u * kPageSize * R + r * R + 16 * (c ^ ((r / P) % C))) =
+                u32x4_t{t[u].k[4 * i], t[u].k[4 * i + 1], t[u].k[4 * i + 2], t[u].k[4 * i + 3]};
+        }
     }
     const int key = (n / P) % C;
 #pragma unroll
-    for (int s = 0; s < (FP8 ? D / 64 : D / 32); ++s) {
-        const int c = FP8 ? quad * (D / 64) + s : 4 * s + quad;
-        kc[s] = *reinterpret_cast<const u32x4_t *>(lds + n * R + 16 * (c ^ key));
+    for (int u = 0; u < NT; ++u) {
+#pragma unroll
+        for (int s = 0; s < (FP8 ? D / 64 : D / 32); ++s) {
+            const int c = FP8 ? quad * (D / 64) + s : 4 * s + quad;
+            kc[u][s] = *reinterpret_cast<const u32x4_t *>(lds + u * kPageSize * R + n * R + 16 * (c ^ key));
+        }
     }
 }
 
@@ -278,39 +326,63 @@ __device__ __forceinline__ void reset(Piece<D> &st)
     st.l = 0.f;
 }
 
-// One tile of the online softmax. `valid` = live tokens in this page (1..16).
-template <int D, bool FP8>
-__device__ __forceinline__ void compute_tile(Piece<D> &st, const Tile<D, FP8> &t,
-                                             const bf16x8_t (&qop)[D / 32], float score_mul,
-                                             int valid, uint8_t *lds, int lane, int n, int quad)
+// One step of the online softmax over NT tiles. `valid` = live tokens of the
+// step (1 .. 16 NT; the first tile has at least one).
+//
+// With several tiles the score products are independent chains, the running
+// maximum is looked at once for all of them, and the value product takes two
+// tiles in one v_mfma_f32_16x16x32_bf16 per 16 columns: its k index 8 quad + i
+// stands for token 4 quad + (i & 3) of tile i / 4 in both operands, so the
+// weights enter exactly as the score MFMAs left them, as with one tile and
+// v_mfma_f32_16x16x16bf16_1k.
+template <int D, bool FP8, int NT>
+__device__ __forceinline__ void compute_step(Piece<D> &st, const Tile<D, FP8> (&t)[NT],
+                                             const bf16x8_t (&qop)[D / 32], float score_mul, int valid, uint8_t *lds,
+                                             int lane, int n, int quad)
 {
-    u32x4_t kc[FP8 ? D / 64 : D / 32];
-    regroup_k<D, FP8>(t, lds, lane, n, quad, kc);
-    f32x4_t s4 = {0.f, 0.f, 0.f, 0.f};
+    static_assert(NT == 1 || NT % 2 == 0, "one tile, or pairs of tiles, per step");
+    u32x4_t kc[NT][FP8 ? D / 64 : D / 32];
+    regroup_k<D, FP8, NT>(t, lds, lane, n, quad, kc);
+    f32x4_t s4[NT];
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+        s4[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < D / 32; ++s)
-        s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand<D, FP8>(kc, s), qop[s], s4, 0, 0, 0);
-
-    float vmul = 1.0f;
-    if constexpr (FP8) {
-        const int bits = __builtin_bit_cast(int, t.scl);
-        score_mul *= __builtin_bit_cast(float, __builtin_amdgcn_readlane(bits, 0));
-        vmul = __builtin_bit_cast(float, __builtin_amdgcn_readlane(bits, 32));
-    }
-    float sc[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        sc[r] = s4[r] * score_mul;
-    if (valid < kPageSize) {
+        for (int u = 0; u < NT; ++u)
+            s4[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand<D, FP8>(kc[u], s), qop[s], s4[u], 0, 0, 0);
+
+    float vmul[NT];
+    float sc[NT][4];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        float mul = score_mul;
+        vmul[u] = 1.0f;
+        if constexpr (FP8) {
+            const int bits = __builtin_bit_cast(int, t[u].scl);
+            mul *= __builtin_bit_cast(float, __builtin_amdgcn_readlane(bits, 0));
+            vmul[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(bits, 32));
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            if (4 * quad + r >= valid)
-                sc[r] = kNegInf;
+            sc[u][r] = s4[u][r] * mul;
     }
-    // The head's maximum over the tile (four lanes) is needed only when one of
+    if (valid < kPageSize * NT) {
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (kPageSize * u + 4 * quad + r >= valid)
+                    sc[u][r] = kNegInf;
+    }
+    // The head's maximum over the step (four lanes) is needed only when one of
     // them exceeds the running maximum by the slack: a wave-wide vote skips
-    // the cross-lane exchange on the other tiles, with the same result.
-    const float lmx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+    // the cross-lane exchange on the other steps, with the same result.
+    float lmx = fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3]));
+#pragma unroll
+    for (int u = 1; u < NT; ++u)
+        lmx = fmaxf(lmx, fmaxf(fmaxf(sc[u][0], sc[u][1]), fmaxf(sc[u][2], sc[u][3])));
     if (__builtin_amdgcn_ballot_w64(lmx > st.m + kRescaleSlack) != 0) {
         const float mx = quad_max(lmx);
         if (mx > st.m + kRescaleSlack) {
@@ -322,10 +394,6 @@ __device__ __forceinline__ void compute_tile(Piece<D> &st, const Tile<D, FP8> &t
             st.m = mx;
         }
     }
-    float pr[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        pr[r] = __builtin_amdgcn_exp2f(sc[r] - st.m);
     // The value product takes the weights rounded to bf16, and the sum of
     // weights adds those same rounded values, so the normalisation cancels
     // their rounding: a token that holds all the weight returns its own value
@@ -334,24 +402,33 @@ __device__ __forceinline__ void compute_tile(Piece<D> &st, const Tile<D, FP8> &t
     // scale, w = bf16(p s); the sum then adds w / s, the rounded weight without
     // the scale (a zero or non-finite scale, for which that quotient is
     // meaningless, adds the rounded p instead).
-    i16x4_t pb;
-    if constexpr (FP8) {
-        const uint32_t w01 = pack_bf16(pr[0] * vmul, pr[1] * vmul);
-        const uint32_t w23 = pack_bf16(pr[2] * vmul, pr[3] * vmul);
-        pb = __builtin_bit_cast(i16x4_t, u32x2_t{w01, w23});
-        const float vinv = __builtin_amdgcn_rcpf(vmul);   // wave-uniform
-        if (__builtin_isfinite(vinv) && vinv != 0.0f) {
-            st.l += ((bf16_lo(w01) + bf16_hi(w01)) + (bf16_lo(w23) + bf16_hi(w23))) * vinv;
+    uint32_t pw[NT][2];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        float pr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            pr[r] = __builtin_amdgcn_exp2f(sc[u][r] - st.m);
+        if constexpr (FP8) {
+            const uint32_t w01 = pack_bf16(pr[0] * vmul[u], pr[1] * vmul[u]);
+            const uint32_t w23 = pack_bf16(pr[2] * vmul[u], pr[3] * vmul[u]);
+            pw[u][0] = w01;
+            pw[u][1] = w23;
+            const float vinv = __builtin_amdgcn_rcpf(vmul[u]);   // wave-uniform
+            if (__builtin_isfinite(vinv) && vinv != 0.0f) {
+                st.l += ((bf16_lo(w01) + bf16_hi(w01)) + (bf16_lo(w23) + bf16_hi(w23))) * vinv;
+            } else {
+                const uint32_t p01 = pack_bf16(pr[0], pr[1]);
+                const uint32_t p23 = pack_bf16(pr[2], pr[3]);
+                st.l += (bf16_lo(p01) + bf16_hi(p01)) + (bf16_lo(p23) + bf16_hi(p23));
+            }
         } else {
             const uint32_t p01 = pack_bf16(pr[0], pr[1]);
             const uint32_t p23 = pack_bf16(pr[2], pr[3]);
             st.l += (bf16_lo(p01) + bf16_hi(p01)) + (bf16_lo(p23) + bf16_hi(p23));
+            pw[u][0] = p01;
+            pw[u][1] = p23;
         }
-    } else {
-        const uint32_t p01 = pack_bf16(pr[0], pr[1]);
-        const uint32_t p23 = pack_bf16(pr[2], pr[3]);
-        st.l += (bf16_lo(p01) + bf16_hi(p01)) + (bf16_lo(p23) + bf16_hi(p23));
-        pb = __builtin_bit_cast(i16x4_t, u32x2_t{p01, p23});
     }
 
     // Value operands. Lane (n, quad) holds D/16 consecutive elements of the
@@ -362,42 +439,66 @@ __device__ __forceinline__ void compute_tile(Piece<D> &st, const Tile<D, FP8> &t
     // sequence's last page) hold arbitrary cache contents and are zeroed first,
     // as 0 * NaN would poison the MFMA.
     constexpr int VR = Tile<D, FP8>::VW / 4;   // dwords per row
-    uint32_t vr[4 * VR];
+    uint32_t vr[NT][4 * VR];
 #pragma unroll
-    for (int k = 0; k < 4 * VR; ++k)
-        vr[k] = t.v[k];
-    if (valid < kPageSize) {
+    for (int u = 0; u < NT; ++u)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int k = 0; k < 4 * VR; ++k)
+            vr[u][k] = t[u].v[k];
+    if (valid < kPageSize * NT) {
 #pragma unroll
-            for (int c = 0; c < VR; ++c)
-                vr[r * VR + c] = 4 * quad + r < valid ? vr[r * VR + c] : 0u;
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < VR; ++c)
+                    vr[u][r * VR + c] = kPageSize * u + 4 * quad + r < valid ? vr[u][r * VR + c] : 0u;
     }
 #pragma unroll
     for (int i = 0; i < D / 16; i += 2) {
-        uint32_t lo0, lo1, hi0, hi1;
-        if constexpr (FP8) {
-            // Bytes (row a, row b) of elements i and i + 1, then one widening per element.
-            const int c = i / 4;
-            const uint32_t sel = (i % 4) == 0 ? 0x05010400u : 0x07030602u;
-            const uint32_t p01 = __builtin_amdgcn_perm(vr[VR + c], vr[c], sel);
-            const uint32_t p23 = __builtin_amdgcn_perm(vr[3 * VR + c], vr[2 * VR + c], sel);
-            lo0 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p01, 1.0f, false));
-            lo1 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p01, 1.0f, true));
-            hi0 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p23, 1.0f, false));
-            hi1 = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p23, 1.0f, true));
-        } else {
-            // Dword w holds elements 2w (low half) and 2w + 1 (high half) of a row.
-            const int w = i / 2;
-            lo0 = __builtin_amdgcn_perm(vr[VR + w], vr[w], 0x05040100u);
-            lo1 = __builtin_amdgcn_perm(vr[VR + w], vr[w], 0x07060302u);
-            hi0 = __builtin_amdgcn_perm(vr[3 * VR + w], vr[2 * VR + w], 0x05040100u);
-            hi1 = __builtin_amdgcn_perm(vr[3 * VR + w], vr[2 * VR + w], 0x07060302u);
+        uint32_t a0[2 * NT], a1[2 * NT];   // operands of blocks i and i + 1
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+            if constexpr (FP8) {
+                // Bytes (row a, row b) of elements i and i + 1, then one widening per element.
+                const int c = i / 4;
+                const uint32_t sel = (i % 4) == 0 ? 0x05010400u : 0x07030602u;
+                const uint32_t p01 = __builtin_amdgcn_perm(vr[u][VR + c], vr[u][c], sel);
+                const uint32_t p23 = __builtin_amdgcn_perm(vr[u][3 * VR + c], vr[u][2 * VR + c], sel);
+                a0[2 * u] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p01, 1.0f, false));
+                a1[2 * u] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p01, 1.0f, true));
+                a0[2 * u + 1] =
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p23, 1.0f, false));
+                a1[2 * u + 1] =
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p23, 1.0f, true));
+            } else {
+                // Dword w holds elements 2w (low half) and 2w + 1 (high half) of a row.
+                const int w = i / 2;
+                a0[2 * u] = __builtin_amdgcn_perm(vr[u][VR + w], vr[u][w], 0x05040100u);
+                a1[2 * u] = __builtin_amdgcn_perm(vr[u][VR + w], vr[u][w], 0x07060302u);
+                a0[2 * u + 1] = __builtin_amdgcn_perm(vr[u][3 * VR + w], vr[u][2 * VR + w], 0x05040100u);
+                a1[2 * u + 1] = __builtin_amdgcn_perm(vr[u][3 * VR + w], vr[u][2 * VR + w], 0x07060302u);
+            }
         }
-        st.acc[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4_t, u32x2_t{lo0, hi0}), pb,
-                                                              st.acc[i], 0, 0, 0);
-        st.acc[i + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4_t, u32x2_t{lo1, hi1}),
-                                                                  pb, st.acc[i + 1], 0, 0, 0);
+        if constexpr (NT > 1) {
+#pragma unroll
+            for (int h = 0; h < NT; h += 2) {
+                const bf16x8_t b =
+                    __builtin_bit_cast(bf16x8_t, u32x4_t{pw[h][0], pw[h][1], pw[h + 1][0], pw[h + 1][1]});
+                st.acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8_t, u32x4_t{a0[2 * h], a0[2 * h + 1], a0[2 * h + 2], a0[2 * h + 3]}), b,
+                    st.acc[i], 0, 0, 0);
+                st.acc[i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8_t, u32x4_t{a1[2 * h], a1[2 * h + 1], a1[2 * h + 2], a1[2 * h + 3]}), b,
+                    st.acc[i + 1], 0, 0, 0);
+            }
+        } else {
+            const i16x4_t b = __builtin_bit_cast(i16x4_t, u32x2_t{pw[0][0], pw[0][1]});
+            st.acc[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                __builtin_bit_cast(i16x4_t, u32x2_t{a0[0], a0[1]}), b, st.acc[i], 0, 0, 0);
+            st.acc[i + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                __builtin_bit_cast(i16x4_t, u32x2_t{a1[0], a1[1]}), b, st.acc[i + 1], 0, 0, 0);
+        }
     }
 }
 
@@ -696,9 +797,10 @@ __device__ __forceinline__ int pages_of(int L, int max_len)
 }
 
 // Plain attention, run by the whole workgroup before its workers start: the
-// pages per sequence, their exclusive prefix sum in s_cum[0 .. B] and the
-// lengths in s_len[0 .. B), all in LDS; workgroup 0 also stores the prefix sum
-// for the merge.
+// steps (of NT pages) per sequence and KV head, their exclusive prefix sum in
+// s_cum[0 .. B] and the lengths in s_len[0 .. B), all in LDS; workgroup 0 also
+// stores the prefix sum for the merge.
+template <int NT>
 __device__ __forceinline__ void scan_sequences(const SplitParams &p, int32_t *s_cum, int32_t *s_len)
 {
     constexpr int T = kWave * kWavesPerBlock;
@@ -707,7 +809,7 @@ __device__ __forceinline__ void scan_sequences(const SplitParams &p, int32_t *s_
     for (int b = threadIdx.x; b < B; b += T) {
         const int L = p.seq_lens[b];
         s_len[b] = L;
-        s_cum[b] = pages_of(L, max_len);
+        s_cum[b] = (pages_of(L, max_len) + NT - 1) / NT;
     }
     __syncthreads();
     block_exclusive_scan(s_cum, B);
@@ -723,7 +825,8 @@ __device__ __forceinline__ void scan_sequences(const SplitParams &p, int32_t *s_
 template <int D, bool FP8>
 __device__ __forceinline__ uint8_t *k_regroup_stage()
 {
-    __shared__ uint8_t k_stage[kWavesPerBlock][kPageSize * D * (FP8 ? 1 : 2)];
+    __shared__ __attribute__((aligned(16)))
+    uint8_t k_stage[kWavesPerBlock][step_tiles<D, FP8>() * kPageSize * D * (FP8 ? 1 : 2)];
     return k_stage[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
 }
 
@@ -732,19 +835,18 @@ constexpr int kAllPages = 0;      // plain attention: every page of every sequen
 constexpr int kOwnPages = 1;      // prefix sharing: the pages after each sequence's shared ones
 constexpr int kSharedPages = 2;   // prefix sharing: each group's shared pages once, one column block per wavefront
 
-// LDS view of the unit stream: the exclusive prefix sum of tiles per sequence
-// and the lengths; for kOwnPages also each sequence's group and the groups'
-// shared-page prefix sum (a sequence's own pages start after its group's
-// shared pages). For kSharedPages `cum` is the shared-page prefix sum over the
-// groups and `gl` each group's first member and size, packed as
-// lead | (members - 1) << 16.
+// LDS view of the unit stream: the exclusive prefix sum of steps per sequence
+// and KV head, and the lengths; for kOwnPages also each sequence's shared pages
+// (its own pages start after them). For kSharedPages the "sequences" are the
+// sub-groups: `cum` is their prefix sum of shared steps and `gl` packs each
+// one's first member, size and the tiles missing from its last step:
+// lead | (members - 1) << 16 | missing << 24.
 struct StreamLds {
-    const int32_t *cum;     // [B + 1], or [NG + 1] for kSharedPages
+    const int32_t *cum;     // [B + 1], or [S + 1] for kSharedPages
     const int32_t *len;     // [B]
-    const int32_t *group;   // [B], kOwnPages only (-1: no shared pages)
-    const int32_t *sh;      // [NG + 1], kOwnPages only
-    const int32_t *gl;      // [NG], kSharedPages only
-    int32_t num_groups;     // kSharedPages only
+    const int32_t *shared;  // [B], kOwnPages only
+    const int32_t *gl;      // [S], kSharedPages only
+    int32_t num_groups;     // S, kSharedPages only
 };
 
 // Worker w of the split-KV pass over the stream that `sv` describes (in LDS,
@@ -755,19 +857,20 @@ template <int D, bool FP8, int MODE>
 __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, const StreamLds &sv, int blk = -1)
 {
     constexpr bool kShared = MODE == kSharedPages;
-    constexpr int kNbuf = pipeline_depth<FP8>();
+    constexpr int kNbuf = kPipelineDepth;
     if (w >= p.num_workers)
         return;
     const int nseq = kShared ? sv.num_groups : p.batch;   // "sequences" of the stream
-    const long long total = (long long)sv.cum[nseq] * p.num_kv_heads;
-    const int nw = effective_workers(total, p.num_workers);
+    constexpr int NT = step_tiles<D, FP8>();
+    const int Hkv = p.num_kv_heads;
+    const long long total = (long long)sv.cum[nseq] * Hkv;
+    const int nw = effective_workers(total, p.num_workers, NT);
     if (w >= nw)
         return;
-    const long long s0 = (long long)w * total / nw;
-    const long long s1 = (long long)(w + 1) * total / nw;
-    if (s0 >= s1)
+    const int s0 = __builtin_amdgcn_readfirstlane((int)((long long)w * total / nw));
+    const int nsteps = __builtin_amdgcn_readfirstlane((int)((long long)(w + 1) * total / nw)) - s0;
+    if (nsteps <= 0)
         return;
-    const int ntiles = (int)(s1 - s0);
     const int lane = threadIdx.x & (kWave - 1);
     const int n = lane & 15;
     const int quad = lane >> 4;
@@ -797,116 +900,94 @@ __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, c
     const int own_slots = kStageOwn ? kOwnStageBytes / part_bytes : 0;   // 1 or more (G <= 16, D <= 128)
     int queued = 0;
 
-    // Tile entries, fetched in tile order (every call below asks for the next
-    // tile; past the range the last tile repeats): {block-table entry (loaded
-    // through a bounds-checked buffer resource), metadata, KV head}, from a
-    // cursor over the units.
-    const __amdgpu_buffer_rsrc_t btab = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int32_t *>(p.block_table), 0, p.batch * p.max_blocks * (int)sizeof(int32_t), kRawBufferWord3);
-    // Cursor: tile (b, g, j) of the stream, the sequence's tile count n_b and
-    // length L_b, and the page index its tiles start at (its group's shared
-    // pages for kOwnPages, else 0).
-    auto shared_of = [&](int b) -> int {
-        if constexpr (MODE == kOwnPages) {
-            const int k = sv.group[b];
-            return k >= 0 ? sv.sh[k + 1] - sv.sh[k] : 0;
-        } else {
-            return 0;
-        }
-    };
-    // Largest b with Hkv cum[b] <= s0 (then its n_b > 0).
-    int blo = 0, bhi = nseq;
-    while (bhi - blo > 1) {
-        const int mid = (blo + bhi) >> 1;
-        if ((long long)sv.cum[mid] * p.num_kv_heads <= s0)
-            blo = mid;
-        else
-            bhi = mid;
-    }
-    int cb = blo;
-    int cnb = sv.cum[cb + 1] - sv.cum[cb];
-    int clen = kShared ? sv.gl[cb] : sv.len[cb];   // kSharedPages: the group's packed lead and size
-    int csh = shared_of(cb);
-    const int off = (int)(s0 - (long long)sv.cum[cb] * p.num_kv_heads);
-    int cg = off / cnb;
-    int cj = off - cg * cnb;
+    // Step descriptors, a chunk of kChunk steps at a time, one step per lane:
+    // lane i finds the unit and the pages of its step in the stream and loads
+    // their block-table entries; the streaming loop then only reads lanes. Per
+    // step that costs two or three lane reads instead of a cursor's compares,
+    // selects and table loads, which at one wavefront per SIMD are time that
+    // nothing else fills. A chunk's table entries are loaded while the chunk
+    // before it streams.
+    constexpr int kChunk = kWave / kNbuf * kNbuf;
+    const __amdgpu_buffer_rsrc_t btab =
+        buffer_of(p.block_table, (uint32_t)(p.batch * p.max_blocks) * (uint32_t)sizeof(int32_t));
     const int max_len = p.max_blocks * kPageSize;
-    auto entry = [&](int i) -> u32x4_t {
-        uint32_t bt, meta;
-        if constexpr (kShared) {
-            // Page cj of the group's shared pages, read through its first member's row; the
-            // count field holds members - 1 (every shared page is full).
-            const int lead = clen & 0xffff;
-            bt = __builtin_bit_cast(
-                uint32_t, __builtin_amdgcn_raw_buffer_load_b32(btab, 0, (lead * p.max_blocks + cj) * 4, 0));
-            meta = (uint32_t)(clen >> 16) | ((uint32_t)(lead * p.num_q_heads + cg * G) << kMetaRowShift);
+    const int top = nseq > 1 ? 1 << (31 - __builtin_clz((unsigned)nseq - 1)) : 0;   // largest power of two below nseq
+    struct Desc {
+        int32_t bt[NT];       // block-table entries (in flight)
+        uint32_t meta;
+        int32_t valid, tiles, g;
+    };
+    auto find = [&](int c0) -> Desc {   // the descriptor of step s0 + c0 + lane (the range's last one past its end)
+        const uint32_t x = (uint32_t)(s0 + min(c0 + lane, nsteps - 1));
+        const int xq = (int)(x / (uint32_t)Hkv);
+        int b = 0;   // largest b with Hkv cum[b] <= x (its steps are not empty)
+        for (int half = top; half > 0; half >>= 1)
+            if (b + half < nseq && sv.cum[b + half] <= xq)
+                b += half;
+        const int first = sv.cum[b], steps = sv.cum[b + 1] - first;
+        const uint32_t off = x - (uint32_t)first * (uint32_t)Hkv;
+        const int g = (int)(off / (uint32_t)steps), j = (int)(off - (uint32_t)g * (uint32_t)steps);
+        Desc d;
+        int row, page;
+        if constexpr (kShared) {   // read through the sub-group's first member's row; every shared page is full
+            const int gl = sv.gl[b];
+            row = gl & 0xffff;
+            page = j * NT;
+            d.tiles = j == steps - 1 ? NT - (gl >> 24) : NT;
+            d.valid = kPageSize * d.tiles | ((gl >> 16) & 15) << 8;
+            d.meta = 0;
         } else {
-            const int pg = csh + cj;   // page index in the sequence
-            bt = __builtin_bit_cast(
-                uint32_t, __builtin_amdgcn_raw_buffer_load_b32(btab, 0, (cb * p.max_blocks + pg) * 4, 0));
-            const int live = min(kPageSize, clen - pg * kPageSize);
-            meta = (uint32_t)(max(live, 1) - 1) | ((uint32_t)(cb * p.num_q_heads + cg * G) << kMetaRowShift);
-            if (clen > max_len)
-                meta |= kMetaBadLen;
-            if (csh > 0)
-                meta |= kMetaPrefixed;
+            const int len = sv.len[b];
+            const int sh = MODE == kOwnPages ? sv.shared[b] : 0;
+            row = b;
+            page = sh + j * NT;
+            d.tiles = min(NT, pages_of(len, max_len) - page);
+            d.valid = max(1, min(kPageSize * d.tiles, len - page * kPageSize));
+            d.meta = (len > max_len ? kMetaBad : 0u) | (sh > 0 ? kMetaPrefixed : 0u);
         }
-        if (cj == 0)
-            meta |= kMetaFirst;
-        if (cj == cnb - 1)
-            meta |= kMetaLast;
-        const u32x4_t e = {bt, meta, (uint32_t)cg, 0u};
-        if (i < ntiles - 1) {   // advance to the next tile of the stream
-            if (++cj == cnb) {
-                cj = 0;
-                if (++cg == p.num_kv_heads) {
-                    cg = 0;
-                    do
-                        ++cb;
-                    while (sv.cum[cb + 1] == sv.cum[cb]);   // tiles remain, so a sequence with tiles follows
-                    cnb = sv.cum[cb + 1] - sv.cum[cb];
-                    clen = kShared ? sv.gl[cb] : sv.len[cb];
-                    csh = shared_of(cb);
-                }
-            }
+        d.g = g;
+        d.meta |= (uint32_t)(row * Hkv + g) << kMetaUnitShift | (j == 0 ? kMetaFirst : 0u) |
+                  (j == steps - 1 ? kMetaLast : 0u);
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+            d.bt[u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(btab, 4 * (row * p.max_blocks + page + u), 0, 0);
+        return d;
+    };
+    int32_t tile[NT];     // per lane: issue_step's T of the lane's step
+    uint32_t lmeta;       // its metadata (kMetaBad also for a page outside the pool)
+    int32_t lvalid;
+    auto settle = [&](const Desc &d) {
+        bool bad = false;
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+            const bool in = (uint32_t)d.bt[u] < (uint32_t)p.num_pages, has = u < d.tiles;
+            const int32_t at = d.bt[u] * Hkv + d.g;
+            tile[u] = has && in ? at : ~(u > 0 ? tile[0] ^ (tile[0] >> 31) : 0);
+            bad |= has && !in;
         }
-        return e;
+        lmeta = d.meta | (bad ? kMetaBad : 0u);
+        lvalid = d.valid;
     };
-    auto page_of = [&](u32x4_t e) -> int32_t {
-        const uint32_t bt = (uint32_t)__builtin_amdgcn_readfirstlane(e[0]);
-        return bt < (uint32_t)p.num_pages ? (int32_t)(bt * (uint32_t)p.num_kv_heads + e[2]) : -1;
+    int cpos = 0, cnext = kChunk;   // lane of the next step to issue; first step of the chunk in `ahead`
+    Desc ahead = find(0);
+    settle(ahead);
+    if (nsteps > kChunk)
+        ahead = find(kChunk);
+    auto issue = [&](Step<D, FP8, NT> &x, int i, bool with_q) {   // step i of the range, from lane cpos
+        int32_t T[NT];
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+            T[u] = __builtin_amdgcn_readlane(tile[u], cpos);
+        x.meta = (uint32_t)__builtin_amdgcn_readlane((int)lmeta, cpos);
+        x.valid = __builtin_amdgcn_readlane(lvalid, cpos);
+        issue_step<D, FP8, NT, !kShared>(x, p, T, i < nsteps, with_q || (x.meta & kMetaFirst) != 0, n, quad, lane, blk);
+        ++cpos;
     };
-    auto meta_of = [](u32x4_t e) { return (uint32_t)__builtin_amdgcn_readfirstlane(e[1]); };
 
-    // Ring of entries: slot k holds the entry of the tile issued at step k (mod
-    // kNbuf). The first entries and the ring are fetched together and waited
-    // for once here (the empty asm consumes them), so that inside the loop the
-    // counter wait for an entry only ever covers the loads of one pipeline turn
-    // and never drains the pipeline.
-    u32x4_t first[kNbuf - 1];
+    Step<D, FP8, NT> buf[kNbuf];
 #pragma unroll
     for (int k = 0; k < kNbuf - 1; ++k)
-        first[k] = entry(k);
-    u32x4_t ring[kNbuf];
-#pragma unroll
-    for (int k = 0; k < kNbuf; ++k)
-        ring[k] = entry(kNbuf - 1 + k);
-#pragma unroll
-    for (int k = 0; k < kNbuf; ++k)
-        asm volatile("" ::"v"(ring[k]));
-    int32_t first_page[kNbuf - 1];
-    uint32_t first_meta[kNbuf - 1];
-#pragma unroll
-    for (int k = 0; k < kNbuf - 1; ++k) {
-        first_page[k] = page_of(first[k]);
-        first_meta[k] = meta_of(first[k]);
-    }
-
-    Tile<D, FP8> buf[kNbuf];
-#pragma unroll
-    for (int k = 0; k < kNbuf - 1; ++k)
-        issue_tile<D, FP8, !kShared>(buf[k], p, first_page[k], first_meta[k],
-                                     k == 0 || (first_meta[k] & kMetaFirst) != 0, n, quad, lane, blk);
+        issue(buf[k], k, k == 0);
 
     Piece<D> st;
     reset(st);
@@ -914,54 +995,58 @@ __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, c
     bool started = false;   // the current unit's first tile is inside this range
     bool bad = false;
     int slot_sel = 0;
-    for (int i0 = 0; i0 < ntiles; i0 += kNbuf) {
+    for (int i0 = 0; i0 < nsteps; i0 += kNbuf) {
 #pragma unroll
         for (int k = 0; k < kNbuf; ++k) {
             const int i = i0 + k;
-            const uint32_t next_meta = meta_of(ring[k]);
-            issue_tile<D, FP8, !kShared>(buf[(k + kNbuf - 1) % kNbuf], p, page_of(ring[k]), next_meta,
-                                         (next_meta & kMetaFirst) != 0, n, quad, lane, blk);
-            ring[k] = entry(i + 2 * kNbuf - 1);
-            if (i < ntiles) {
-                const Tile<D, FP8> &t = buf[k];
+            if (k == 1 && cpos == kChunk) {   // (the step issued at k == 1 is a multiple of kNbuf)
+                settle(ahead);
+                cpos = 0;
+                cnext += kChunk;
+                if (cnext < nsteps)
+                    ahead = find(cnext);
+            }
+            issue(buf[(k + kNbuf - 1) % kNbuf], i + kNbuf - 1, false);
+            if (i < nsteps) {
+                const Step<D, FP8, NT> &t = buf[k];
                 const uint32_t meta = t.meta;
+                const bool ends = i == nsteps - 1;
                 if (i == 0 || (meta & kMetaFirst) != 0) {
 #pragma unroll
                     for (int s = 0; s < D / 32; ++s)
-                        qop[s] = __builtin_bit_cast(bf16x8_t,
-                                                    kShared || n < G ? t.q[s] : u32x4_t{0u, 0u, 0u, 0u});
+                        qop[s] = __builtin_bit_cast(bf16x8_t, t.q[s]);
                 }
                 started |= (meta & kMetaFirst) != 0;
-                bad |= t.bad_page || (meta & kMetaBadLen) != 0;
-                compute_tile<D, FP8>(st, t, qop, p.scale_log2, kShared ? kPageSize : (int)(meta & 15u) + 1, lds,
-                                     lane, n, quad);
-                if (kShared && ((meta & kMetaLast) != 0 || i == ntiles - 1)) {
+                bad |= (meta & kMetaBad) != 0;
+                compute_step<D, FP8, NT>(st, t.t, qop, p.scale_log2, kShared ? t.valid & 0xff : t.valid, lds, lane, n,
+                                         quad);
+                if (kShared && ((meta & kMetaLast) != 0 || ends)) {
                     // A shared unit's state is always merged: a whole one goes to the unit area
                     // (indexed by first query row / G), a cut one to the worker's slot; block blk
                     // holds rows 16 blk .. 16 blk + 15 of the unit's kPrefixRows.
-                    const uint32_t row0 = meta >> kMetaRowShift;
+                    const uint32_t unit = meta >> kMetaUnitShift;
                     const bool whole = started && (meta & kMetaLast) != 0;
-                    const size_t slot = whole ? (size_t)(row0 / (uint32_t)G) : 2 * (size_t)w + slot_sel;
+                    const size_t slot = whole ? (size_t)unit : 2 * (size_t)w + slot_sel;
                     const int r = 16 * blk + n;
                     const float l = quad_sum(st.l);
-                    if (r < ((int)(meta & 15u) + 1) * G)
+                    if (r < ((t.valid >> 8) + 1) * G)
                         store_partial<D>(st, l, bad, whole ? p.unit_ml : p.part_ml, whole ? p.unit_acc : p.part_acc,
                                          slot * kPrefixRows + r, quad);
                     reset(st);
                     started = false;
                     bad = false;
                     slot_sel = 1;
-                } else if (!kShared && ((meta & kMetaLast) != 0 || i == ntiles - 1)) {
+                } else if (!kShared && ((meta & kMetaLast) != 0 || ends)) {
                     // A unit cut by this range leaves its piece in the worker's slot 2w + slot_sel.
                     // A whole unit is written out, unless it still has to be merged (shared pages,
                     // or the own pages of a sequence that has them): then its state goes to its
                     // own slot in the unit area, indexed by (first query row) / G.
-                    const uint32_t row0 = meta >> kMetaRowShift;
+                    const uint32_t unit = meta >> kMetaUnitShift, row0 = unit * (uint32_t)G;
                     const bool whole = started && (meta & kMetaLast) != 0;
                     const bool to_unit = whole && (meta & kMetaPrefixed) != 0;
                     float *const pml = to_unit ? p.unit_ml : p.part_ml;
                     float *const pacc = to_unit ? p.unit_acc : p.part_acc;
-                    const size_t slot = to_unit ? (size_t)(row0 / (uint32_t)G) : 2 * (size_t)w + slot_sel;
+                    const size_t slot = to_unit ? (size_t)unit : 2 * (size_t)w + slot_sel;
                     if (kStageOut && whole) {
                         const float l = quad_sum(st.l);
                         if (n < G)

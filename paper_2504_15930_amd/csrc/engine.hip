@@ -75,13 +75,11 @@ __global__ __launch_bounds__(kEngineThreads) void engine_fill_kernel(const int32
 // the bookkeeping.
 
 constexpr int kUnitThreads = kUnitWaves * kWave;
-template <bool FP8>
-constexpr int unit_depth() { return FP8 ? 3 : 2; }   // tiles in flight per wave (as the split kernel)
 
 // LDS of an attention workgroup: the waves' K regroup stages (sized for
 // bf16 tiles, which E4M3 tiles fit), then every wave's final state,
-// lane-major (D / 4 accumulator values, m and l per lane): 100 KB for D = 128, which gfx950's 160 KB of LDS per CU holds (the
-// kernel's registers allow one such workgroup per CU anyway).
+// lane-major (D / 4 accumulator values, m and l per lane): 100 KB for D = 128,
+// which gfx950's 160 KB of LDS per CU holds.
 template <int D>
 constexpr int unit_state_floats() { return D / 4 + 2; }
 template <int D>
@@ -115,8 +113,20 @@ __device__ __forceinline__ f32x2_t load2_device(__amdgpu_buffer_rsrc_t r, int of
     return __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kCachePolicyDevice));
 }
 
+// This lane's part of the argument arrays, fetched before anything else so
+// that it arrives together with the scalar arguments.
+struct UnitArgs {
+    int32_t f_lo, f_hi, seq_lo, seq_hi, len_lo, len_hi;
+};
+__device__ __forceinline__ UnitArgs unit_args(const UnitStepParams &up, int lane)
+{
+    return UnitArgs{up.first[lane + 1], up.first[lane + 1 + kWave], up.seq[lane],
+                    up.seq[lane + kWave], up.len[lane],             up.len[lane + kWave]};
+}
+
 template <int D, bool FP8>
-__device__ __forceinline__ void unit_attention(const UnitStepParams &up, int blk, uint8_t *smem, int32_t *s_last)
+__device__ __forceinline__ void unit_attention(const UnitStepParams &up, const UnitArgs &ar, int blk, uint8_t *smem,
+                                               int32_t *s_last)
 {
     const SplitParams &p = up.cur;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -124,21 +134,21 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, int blk
     const int n = lane & 15, quad = lane >> 4;
     const int G = p.group, Hkv = p.num_kv_heads;
 
-    // Entry e with first[e] <= blk < first[e + 1], head g and piece k.
-    int lo = 0, hi = up.n_entries;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (up.first[mid] <= blk)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    const int e = lo;
-    const int K = (up.first[e + 1] - up.first[e]) / Hkv;
-    const int local = blk - up.first[e];
+    // Entry e with first[e] <= blk < first[e + 1], head g and piece k: the
+    // argument arrays, read by all lanes at once, are searched in registers (a
+    // binary search over them is a chain of dependent loads).
+    static_assert(kMaxUnitEntries == 2 * kWave, "the argument arrays are read in two halves");
+    const int e = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < up.n_entries && ar.f_lo <= blk)) +
+                  __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane + kWave < up.n_entries && ar.f_hi <= blk));
+    auto pick = [](int lo, int hi, int i) {
+        return i < kWave ? __builtin_amdgcn_readlane(lo, i & (kWave - 1)) : __builtin_amdgcn_readlane(hi, i & (kWave - 1));
+    };
+    const int first_e = e > 0 ? pick(ar.f_lo, ar.f_hi, e - 1) : 0;
+    const int K = (pick(ar.f_lo, ar.f_hi, e) - first_e) / Hkv;
+    const int local = blk - first_e;
     const int g = local / K, k = local - g * K;
-    const int b = up.seq[e];
-    const int L = up.len[e];
+    const int b = pick(ar.seq_lo, ar.seq_hi, e);
+    const int L = pick(ar.len_lo, ar.len_hi, e);
     const int max_len = p.max_blocks * kPageSize;
     const int Lc = min(L, max_len);
     const int nb = pages_of(L, max_len);
@@ -150,11 +160,12 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, int blk
         return;
     }
 
-    // This wave's tiles [t0, t1) of the unit.
-    const long long waves = (long long)K * kUnitWaves;
-    const int gw = k * kUnitWaves + wave;
-    const int t0 = (int)((long long)gw * nb / waves);
-    const int nt = (int)((long long)(gw + 1) * nb / waves) - t0;
+    // This wave's tiles [t0, t0 + nt) of the unit: floor(gw nb / waves) ..
+    // floor((gw + 1) nb / waves), without the wide product.
+    const unsigned waves = (unsigned)K * kUnitWaves, gw = (unsigned)k * kUnitWaves + wave;
+    const unsigned per = (unsigned)nb / waves, rem = (unsigned)nb % waves;
+    const int t0 = (int)(gw * per + gw * rem / waves);
+    const int nt = (int)((gw + 1) * per + (gw + 1) * rem / waves) - t0;
 
     Piece<D> st;
     reset(st);
@@ -162,48 +173,46 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, int blk
     if (nt > 0) {
         uint8_t *lds = smem + wave * (kPageSize * D * 2);
         const int32_t *bt_row = p.block_table + (size_t)b * p.max_blocks + t0;
-        // The query rows (lanes past the group read row G - 1 and use zeros)
-        // and the first 64 block-table entries of the range, issued together.
-        bf16x8_t qop[D / 32];
-        {
-            const uint16_t *qrow = p.q + ((size_t)row0 + (size_t)min(n, G - 1)) * D;
+        const __amdgpu_buffer_rsrc_t ids_rsrc = buffer_of(bt_row, (uint32_t)nt * 4u);
+        int32_t ids = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(ids_rsrc, 4 * lane, 0, 0);
+        u32x4_t qop[D / 32];
+        load_q<D, FP8>(qop, p, row0, true, n, quad);
+        // Chunks of up to 64 tiles, whose block-table entries a wave holds in
+        // one register; kDepth tiles in flight within a chunk (one to six
+        // measured the same or slower, as did two tiles per step: a wave has
+        // three tiles or so, and an odd one costs a whole step). The ids are
+        // not loaded inside the tile loop: a load on some iterations only
+        // would make every iteration wait for all tiles in flight.
+        constexpr int kDepth = kPipelineDepth;
+        for (int c0 = 0; c0 < nt; c0 += kWave) {
+            const int cn = min(kWave, nt - c0);
+            if (c0 > 0)
+                ids = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(ids_rsrc, 4 * (c0 + lane), 0, 0);
+            // Per lane: issue_step's tile index of tile c0 + lane of the range.
+            const bool in = (uint32_t)ids < (uint32_t)p.num_pages;
+            const int32_t tile = in ? ids * Hkv + g : ~0;
+            bad |= __builtin_amdgcn_ballot_w64(!in && lane < cn) != 0;
+            auto issue = [&](Tile<D, FP8> (&t)[1], int i) {   // tile c0 + i of the range, if there is one
+                const int32_t T = __builtin_amdgcn_readlane(tile, i & (kWave - 1));
+                issue_tile<D, FP8, true>(t[0], p, (uint32_t)(T ^ (T >> 31)), i < cn && T >= 0, n, quad, lane);
+            };
+            Tile<D, FP8> buf[kDepth][1];
+            bf16x8_t qb[D / 32];
 #pragma unroll
-            for (int s = 0; s < D / 32; ++s) {
-                const u32x4_t x = ld128(reinterpret_cast<const uint8_t *>(qrow + q_index<D, FP8>(s, quad)));
-                qop[s] = __builtin_bit_cast(bf16x8_t, n < G ? x : u32x4_t{0u, 0u, 0u, 0u});
-            }
-        }
-        int32_t ids = lane < nt ? bt_row[lane] : 0;
-        auto page_at = [&](int i) -> int32_t {   // tile i of the range; its entry is in `ids`
-            const uint32_t v = (uint32_t)__builtin_amdgcn_readlane(ids, i & (kWave - 1));
-            return v < (uint32_t)p.num_pages ? (int32_t)(v * (uint32_t)Hkv + (uint32_t)g) : -1;
-        };
-        auto meta_at = [&](int i) -> uint32_t {
-            const int live = min(kPageSize, Lc - (t0 + i) * kPageSize);   // >= 1: t0 + i < nb
-            return (uint32_t)(live - 1) | (row0 << kMetaRowShift);
-        };
-        // kDepth tiles in flight.
-        constexpr int kDepth = unit_depth<FP8>();
-        Tile<D, FP8> buf[kDepth];
+            for (int s = 0; s < D / 32; ++s)
+                qb[s] = __builtin_bit_cast(bf16x8_t, qop[s]);
 #pragma unroll
-        for (int k0 = 0; k0 < kDepth - 1; ++k0)
-            if (k0 < nt)
-                issue_tile<D, FP8>(buf[k0], p, page_at(k0), meta_at(k0), false, n, quad, lane);
-        for (int i0 = 0; i0 < nt; i0 += kDepth) {
+            for (int k0 = 0; k0 < kDepth - 1; ++k0)
+                issue(buf[k0], k0);
+            for (int i0 = 0; i0 < cn; i0 += kDepth) {
 #pragma unroll
-            for (int kk = 0; kk < kDepth; ++kk) {
-                const int i = i0 + kk;
-                if (i < nt) {
-                    const int ia = i + kDepth - 1;   // the tile issued now
-                    if (ia < nt) {
-                        if ((ia & (kWave - 1)) == 0)     // the next 64 entries
-                            ids = lane < nt - ia ? bt_row[ia + lane] : 0;
-                        issue_tile<D, FP8>(buf[(kk + kDepth - 1) % kDepth], p, page_at(ia), meta_at(ia), false, n,
-                                           quad, lane);
+                for (int kk = 0; kk < kDepth; ++kk) {
+                    const int i = i0 + kk;
+                    issue(buf[(kk + kDepth - 1) % kDepth], i + kDepth - 1);
+                    if (i < cn) {
+                        const int live = min(kPageSize, Lc - (t0 + c0 + i) * kPageSize);   // >= 1: t0 + c0 + i < nb
+                        compute_step<D, FP8, 1>(st, buf[kk], qb, p.scale_log2, live, lds, lane, n, quad);
                     }
-                    const Tile<D, FP8> &t = buf[kk];
-                    bad |= t.bad_page;
-                    compute_tile<D, FP8>(st, t, qop, p.scale_log2, (int)(t.meta & 15u) + 1, lds, lane, n, quad);
                 }
             }
         }
@@ -214,6 +223,7 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, int blk
     constexpr int SF = unit_state_floats<D>();
     float *const states = reinterpret_cast<float *>(smem + unit_stage_bytes<D>());
     {
+        const float lsum = quad_sum(st.l);
         float *dst = states + (size_t)wave * SF * kWave + lane;
 #pragma unroll
         for (int i = 0; i < D / 16; ++i)
@@ -221,59 +231,51 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, int blk
             for (int r = 0; r < 4; ++r)
                 dst[(4 * i + r) * kWave] = st.acc[i][r];
         dst[(D / 4) * kWave] = st.m;
-        dst[(D / 4 + 1) * kWave] = st.l;
+        dst[(D / 4 + 1) * kWave] = lsum;
     }
     const bool bad_any = __syncthreads_or(bad ? 1 : 0) != 0;
     const float poison = bad_any ? __builtin_nanf("") : 0.0f;
 
     // Combine the kUnitWaves states, in wave order (so the result does not
-    // depend on timing): thread t = (16 n + 4 quad + r) takes lane
-    // (n, quad)'s accumulator values 4 i + r, i = 0 .. D/16 - 1, which are
-    // the D/16 consecutive columns quad D/4 + r D/16 + i of row n.
+    // depend on timing). An item is four consecutive columns of one row: lane
+    // (n, quad)'s accumulator values 4 i + r for i = 4 c .. 4 c + 3 are the
+    // columns quad D/4 + r D/16 + 4 c + 0..3 of row n. Consecutive threads
+    // take consecutive rows, whose values lie in consecutive banks.
     const int unit = e * Hkv + g;
     const int mls = unit_ml_stride(G);
     const __amdgpu_buffer_rsrc_t ml_rsrc = piece_rsrc(p.part_ml, sizeof(float) * kMaxUnitBlocks * mls);
     const __amdgpu_buffer_rsrc_t acc_rsrc = piece_rsrc(p.part_acc, sizeof(float) * kMaxUnitBlocks * G * D);
-    const int t = threadIdx.x;
-    if (t < 16 * G) {
-        const int cn = t >> 4, cq = (t >> 2) & 3, cr = t & 3;
-        const int cl = cn + 16 * cq;   // source lane
-        float m[kUnitWaves], ls[kUnitWaves];
-        float M = kNegInf;
+    for (int item = threadIdx.x; item < G * (D / 4); item += kUnitThreads) {
+        const int cn = item % G, w4 = item / G;              // row; (c, r, quad) of its columns
+        const int cq = w4 & 3, cr = (w4 >> 2) & 3, c = w4 >> 4;
+        const int cl = cn + 16 * cq;                         // source lane
+        const float *src = states + (16 * c + cr) * kWave + cl;
+        float m[kUnitWaves], ls[kUnitWaves], x[kUnitWaves][4];
 #pragma unroll
         for (int w = 0; w < kUnitWaves; ++w) {
-            const float *src = states + (size_t)w * SF * kWave;
-            m[w] = src[(D / 4) * kWave + cl];
-            ls[w] = (src[(D / 4 + 1) * kWave + cn] + src[(D / 4 + 1) * kWave + cn + 16]) +
-                    (src[(D / 4 + 1) * kWave + cn + 32] + src[(D / 4 + 1) * kWave + cn + 48]);
+            m[w] = states[((size_t)w * SF + D / 4) * kWave + cl];
+            ls[w] = states[((size_t)w * SF + D / 4 + 1) * kWave + cl];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                x[w][i] = src[((size_t)w * SF + 4 * i) * kWave];
+        }
+        float M = m[0];
+#pragma unroll
+        for (int w = 1; w < kUnitWaves; ++w)
             M = fmaxf(M, m[w]);
-        }
-        float L = 0.0f;
-        float a[D / 16];
-#pragma unroll
-        for (int i = 0; i < D / 16; ++i)
-            a[i] = 0.0f;
+        float l = 0.0f;
+        f32x4_t a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < kUnitWaves; ++w) {
-            const float c = m[w] == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(m[w] - M);
-            const float *src = states + (size_t)w * SF * kWave + cl;
-            L += c * ls[w];
-#pragma unroll
-            for (int i = 0; i < D / 16; ++i)
-                a[i] += c * src[(4 * i + cr) * kWave];
+            const float wt = m[w] == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(m[w] - M);
+            l += wt * ls[w];
+            a += wt * f32x4_t{x[w][0], x[w][1], x[w][2], x[w][3]};
         }
-        const int col = cq * (D / 4) + cr * (D / 16);
-        if (K == 1) {   // the whole unit: normalise and write the row's D/16 columns
-            const float inv = bad_any ? __builtin_nanf("") : 1.0f / L;
-            uint32_t wv[D / 32];
-#pragma unroll
-            for (int h = 0; h < D / 32; ++h)
-                wv[h] = pack_bf16(a[2 * h] * inv, a[2 * h + 1] * inv);
-            uint16_t *dst = p.out + ((size_t)row0 + cn) * D + col;
-            if constexpr (D == 128)
-                *reinterpret_cast<u32x4_t *>(dst) = u32x4_t{wv[0], wv[1], wv[2], wv[3]};
-            else
-                *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{wv[0], wv[1]};
+        const int col = cq * (D / 4) + cr * (D / 16) + 4 * c;
+        if (K == 1) {   // the whole unit: normalise and write the columns
+            const float inv = bad_any ? __builtin_nanf("") : 1.0f / l;
+            *reinterpret_cast<u32x2_t *>(p.out + ((size_t)row0 + cn) * D + col) =
+                u32x2_t{pack_bf16(a[0] * inv, a[1] * inv), pack_bf16(a[2] * inv, a[3] * inv)};
         } else {
             // A piece goes to slot blk; the last of the unit's K workgroups
             // to arrive merges them. The pieces cross XCDs, whose L2 caches
@@ -283,19 +285,14 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, int blk
             // agent-scope fence would do the same by writing back, or
             // invalidating, the whole L2 of the XCD, at several microseconds
             // per workgroup.
-            const int off = (blk * G + cn) * D + col;
-#pragma unroll
-            for (int i = 0; i < D / 16; i += 4)
-                store4_device(acc_rsrc, 4 * (off + i),
-                              f32x4_t{a[i], a[i + 1], a[i + 2], a[i + 3]} + poison);
-            if (cq == 0 && cr == 0)
-                store2_device(ml_rsrc, 4 * (blk * mls + 2 * cn), f32x2_t{M + poison, L});
+            store4_device(acc_rsrc, 4 * ((blk * G + cn) * D + col), a + poison);
+            if (w4 == 0)
+                store2_device(ml_rsrc, 4 * (blk * mls + 2 * cn), f32x2_t{M + poison, l});
         }
     }
-    // The unit's next-step row, by the last wave (which has no combine work
-    // for any G <= 16: the combine takes threads below 16 G): with one
-    // workgroup per unit, every wave's reads of the unit's pages are done
-    // once the barrier above has passed.
+    // The unit's next-step row, by the last wave: with one workgroup per unit,
+    // every wave's reads of the unit's pages are done once the barrier above
+    // has passed.
     const bool tail_append = up.units_append && wave == kUnitWaves - 1;
     if (K == 1) {
         if (tail_append)
@@ -395,9 +392,10 @@ __global__ __launch_bounds__(kUnitThreads) void engine_unit_step_kernel(UnitStep
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[unit_smem_bytes<D>()];
     __shared__ int32_t s_last;
+    const UnitArgs ar = unit_args(up, threadIdx.x & (kWave - 1));
     int blk = (int)blockIdx.x;
     if (blk < up.unit_blocks) {
-        unit_attention<D, FP8>(up, blk, smem, &s_last);
+        unit_attention<D, FP8>(up, ar, blk, smem, &s_last);
         return;
     }
     blk -= up.unit_blocks;

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p, int
             dst[e] = fill;
         return;
     }
-    const long long NW = effective_workers(total, p.num_workers);
+    const long long NW = effective_workers(total, p.num_workers, p.step_tiles);
     const long long a = (long long)Hkv * cb + (long long)g * nb;   // first tile of the unit
     const long long e = a + nb;                                    // one past its last tile
     // Worker holding tile x: the largest w with floor(w * total / NW) <= x.
@@ -218,8 +218,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
     const int lane = threadIdx.x & (kWave - 1);
     uint16_t *dst = p.out + ((size_t)b * Hq + h) * D + E * lane;
     // First round trip: the sequence's place in both tile streams.
-    const int32_t *info = p.seq_shared + 4 * (size_t)b;   // shared-page start, count, lead, group
-    const int s_start = info[0], sk = info[1], lead = info[2];
+    const int32_t *info = p.seq_shared + 4 * (size_t)b;   // first shared step, shared pages, lead, shared steps
+    const int s_start = info[0], sk = info[1], lead = info[2], ss = info[3];
     const int L = p.seq_lens[b];
     const int co = p.cum_own[b];
     const int ob = p.cum_own[b + 1] - co;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
             dst[e] = fill;
         return;
     }
-    const long long nw_o = effective_workers(tot_o, p.num_workers);
+    const long long nw_o = effective_workers(tot_o, p.num_workers, p.step_tiles);
     const long long a_o = (long long)Hkv * co + (long long)g * ob;
     int wf_o = 0, n_o = 0;
     if (ob > 0) {
@@ -243,15 +243,17 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
     if (sk == 0 && n_o == 1)
         return;   // finished by a single worker
     const long long nw_s =
-        tot_s > 0 ? effective_workers(tot_s, effective_shared_workers(tot_o, p.num_workers, p.num_shared_workers,
-                                                                      p.max_shared_workers))
+        tot_s > 0 ? effective_workers(tot_s,
+                                      effective_shared_workers(tot_o, p.num_workers, p.num_shared_workers,
+                                                               p.max_shared_workers, p.step_tiles),
+                                      p.step_tiles)
                   : 1;
     long long a_s = 0;
     int wf_s = 0, n_s = 0, row = 0;
     if (sk > 0) {
-        a_s = (long long)Hkv * s_start + (long long)g * sk;
+        a_s = (long long)Hkv * s_start + (long long)g * ss;
         wf_s = (int)div_floor((a_s + 1) * nw_s - 1, tot_s);
-        n_s = (int)div_floor((a_s + sk) * nw_s - 1, tot_s) - wf_s + 1;
+        n_s = (int)div_floor((a_s + ss) * nw_s - 1, tot_s) - wf_s + 1;
         row = (b - lead) * G + hl;
     }
     const int np = n_s + n_o;

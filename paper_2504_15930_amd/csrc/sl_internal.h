@@ -53,11 +53,12 @@ constexpr int kMaxWorkers = 1 << 16;       // keeps partial-state offsets below 
 // one or two tiles, each of which would cost a partial state and a merge step.
 constexpr int kMinTilesPerWorker = SL_MIN_TILES_PER_WORKER;
 
-// Workers that take part in a stream of `total` tiles (the others exit at
-// once); both the split kernel and the merge derive it from the same total.
-__host__ __device__ inline int effective_workers(long long total, int num_workers)
+// Workers that take part in a stream of `total` steps of step_tiles tiles (the
+// others exit at once); both the split kernel and the merge derive it from the
+// same total.
+__host__ __device__ inline int effective_workers(long long total, int num_workers, int step_tiles)
 {
-    const long long want = (total + kMinTilesPerWorker - 1) / kMinTilesPerWorker;
+    const long long want = (total * step_tiles + kMinTilesPerWorker - 1) / kMinTilesPerWorker;
     return want < 1 ? 1 : (want < num_workers ? (int)want : num_workers);
 }
 // Prefix sharing: shared-page workgroups that take part in a call. The launch
@@ -67,36 +68,36 @@ __host__ __device__ inline int effective_workers(long long total, int num_worker
 // few own pages still streams its shared pages with two workgroups per CU.
 // The split kernel and the merge derive it from the same totals (own tiles).
 __host__ __device__ inline int effective_shared_workers(long long own_total, int own_workers, int base,
-                                                        int max_workers)
+                                                        int max_workers, int step_tiles)
 {
     const int own_blocks = (own_workers + kWavesPerBlock - 1) / kWavesPerBlock;
     const int active =
-        own_total > 0 ? (effective_workers(own_total, own_workers) + kWavesPerBlock - 1) / kWavesPerBlock : 0;
+        own_total > 0 ? (effective_workers(own_total, own_workers, step_tiles) + kWavesPerBlock - 1) / kWavesPerBlock : 0;
     const int idle = own_blocks - active;
     const int n = base + (idle < base ? idle : base);
     return n < max_workers ? n : max_workers;
 }
 constexpr size_t kAlign = 256;
 
-// Tile metadata, one wave-uniform word per tile, from bit 0:
-//   [3:0] live tokens in the tile minus one, [4] last tile of its unit,
-//   [5] first tile of its unit, [6] the sequence length is invalid,
-//   [7] see kMetaPrefixed, [31:8] first query row of the unit, b * Hq + g * G.
+// Step metadata, one word per step of a stream:
+//   [4] last step of its unit, [5] first step of its unit, [6] the sequence
+//   length is invalid or the block table named a page outside the pool,
+//   [7] see kMetaPrefixed, [31:8] the unit, b * Hkv + g (its first query row
+//   over G).
 // A tile's KV data is page-head tile page_id * Hkv + g of the
-// [num_pages][Hkv] grid (-1: the block table named a page outside the pool).
+// [num_pages][Hkv] grid.
 constexpr uint32_t kMetaLast = 1u << 4;
 constexpr uint32_t kMetaFirst = 1u << 5;
-constexpr uint32_t kMetaBadLen = 1u << 6;
+constexpr uint32_t kMetaBad = 1u << 6;
 constexpr uint32_t kMetaPrefixed = 1u << 7;   // own-page unit of a sequence whose first pages are shared
 // Prefix-sharing mode: the shared-page stream holds, per (group, KV head),
-// the group's shared pages once; their metadata keeps members - 1 in bits [3:0]
-// (every shared page is full) and the first query row of the group's first
-// member in [31:8]. The query rows of a shared unit are (member j, head h) ->
+// the group's shared pages once (every shared page is full); their metadata
+// names the unit of the group's first member. The query rows of a shared unit are (member j, head h) ->
 // row0 + j * Hq + h, at most kPrefixRows of them (kPrefixBlocks MFMA column
 // blocks of 16).
 constexpr int kPrefixBlocks = 4;
 constexpr int kPrefixRows = 16 * kPrefixBlocks;
-constexpr int kMetaRowShift = 8;
+constexpr int kMetaUnitShift = 8;
 
 struct Workspace {
     int32_t *cum_pages;   // [B + 1] exclusive prefix sum of pages per sequence (written by the split kernel)
@@ -139,10 +140,10 @@ struct SplitParams {
 struct PrefixParams {
     const int32_t *group_start;   // [num_groups + 1]
     const int32_t *shared_pages;  // [num_groups]
-    int32_t *cum_own;             // [B + 1] prefix sum of own (unshared) pages
-    int32_t *cum_shared;          // [max_sub + 1] prefix sum of shared pages per sub-group
-    int32_t *seq_shared;          // [B][4] per sequence: first shared page of its sub-group in the shared
-                                  // stream, shared pages, sub-group's first member, sub-group (-1, zeros if
+    int32_t *cum_own;             // [B + 1] prefix sum of steps over own (unshared) pages
+    int32_t *cum_shared;          // [max_sub + 1] prefix sum of steps over shared pages per sub-group
+    int32_t *seq_shared;          // [B][4] per sequence: first shared step of its sub-group in the shared
+                                  // stream, shared pages, sub-group's first member, shared steps (zeros if
                                   // unshared)
     int32_t num_groups;
     int32_t max_sub;              // prefix_max_sub: bound on the sub-groups (shared-stream "sequences")
@@ -177,6 +178,7 @@ struct PrefixMergeParams {
     int32_t batch, max_sub, num_q_heads, num_kv_heads, group, num_workers, max_blocks;
     int32_t num_shared_workers;   // base and largest count of shared-page workgroups
     int32_t max_shared_workers;   // (effective_shared_workers)
+    int32_t step_tiles;           // as the split kernel's
 };
 
 struct AppendParams {
@@ -208,6 +210,7 @@ struct MergeParams {
     const float *part_acc;
     uint16_t *out;
     int32_t batch, num_q_heads, num_kv_heads, group, num_workers;
+    int32_t step_tiles;   // as the split kernel's
     // Decode engine: the next step's staged append (and its bookkeeping) runs
     // in the same launch, in workgroups after the merge's; 0 none, 1 bf16
     // cache, 2 E4M3 cache. The merge never reads what it writes: it reads the
@@ -257,6 +260,8 @@ hipError_t launch_append(const AppendParams &p, int head_dim, bool fp8, hipStrea
 // Decode engine helper (engine.hip): fill prompt pages with synthetic data.
 hipError_t launch_engine_fill(const int32_t *pages, int n_pages, int hkv, int head_dim, bool fp8, uint32_t seed,
                               void *k_pages, void *v_pages, float *k_scales, float *v_scales, hipStream_t stream);
+// Pages per pipeline step of the split kernels (their streams are counted in steps).
+int split_step_tiles(int head_dim, bool fp8);
 // Resident split-kernel workgroups per CU (occupancy query), for the default worker count.
 hipError_t split_blocks_per_cu(int head_dim, bool fp8, int *blocks);
 
