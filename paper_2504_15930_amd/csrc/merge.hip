@@ -10,11 +10,17 @@
 //
 // One wavefront per (unit, query head). Lane i first fetches (m_i, l_i) of
 // piece i, so the maximum, the weights c_i = 2^(m_i - M) and their weighted
-// sum come out of two wave reductions instead of a serial walk; then every
-// lane accumulates its D/64 output columns over the pieces with independent
-// loads. Units finished by a single worker were already written and are
-// skipped. Sequences without pages get zero rows (NaN rows for an invalid
-// negative length), which no split-KV worker visits.
+// sum come out of two wave reductions instead of a serial walk. The rows are
+// read as four columns per lane, D/4 lanes per row and so 256/D rows per load
+// instruction, several loads in flight (combine_pieces): bound by the latency
+// of its few dependent loads, and with long units, cut across dozens of
+// workers, by how many of their rows are in flight. Units finished by a single
+// worker were already written and are skipped. Sequences without pages get
+// zero rows (NaN rows for an invalid negative length), which no split-KV
+// worker visits.
+//
+// Measured (MI355X): five sequences of 2K..16K tokens, units of up to 68
+// pieces: 5.3 us (one row per iteration: 18.0).
 #include "append_unit.h"
 
 namespace sl {
@@ -23,20 +29,106 @@ namespace {
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+
+// One step of a wave reduction: the value of the lane that the DPP control
+// names, or `none` where there is no such lane or its row is masked out.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float lane_from(float x, float none)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none),
+                                                                 __builtin_bit_cast(int, x), CTRL, ROWS, 0xf, false));
+}
+// Reductions over the wavefront, the result in every lane: shifts by 1, 2, 4
+// and 8 within rows of 16 lanes, then the row totals passed on (a vector
+// instruction each, where a shuffle is a round trip through LDS).
 __device__ __forceinline__ float wave_max(float x)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        x = fmaxf(x, __shfl_xor(x, off, kWave));
-    return x;
+    constexpr float kNone = -__builtin_inff();
+    x = fmaxf(x, lane_from<0x111, 0xf>(x, kNone));
+    x = fmaxf(x, lane_from<0x112, 0xf>(x, kNone));
+    x = fmaxf(x, lane_from<0x114, 0xf>(x, kNone));
+    x = fmaxf(x, lane_from<0x118, 0xf>(x, kNone));
+    x = fmaxf(x, lane_from<0x142, 0xa>(x, kNone));
+    x = fmaxf(x, lane_from<0x143, 0xc>(x, kNone));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), kWave - 1));
 }
-
 __device__ __forceinline__ float wave_sum(float x)
 {
+    x += lane_from<0x111, 0xf>(x, 0.0f);
+    x += lane_from<0x112, 0xf>(x, 0.0f);
+    x += lane_from<0x114, 0xf>(x, 0.0f);
+    x += lane_from<0x118, 0xf>(x, 0.0f);
+    x += lane_from<0x142, 0xa>(x, 0.0f);
+    x += lane_from<0x143, 0xc>(x, 0.0f);
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), kWave - 1));
+}
+
+// Combine the np >= 1 pieces of one row: ml_of(i) and acc_of(i) give the
+// addresses of piece i's (m, l) pair and of its D accumulators. Every lane
+// gets four columns, c4 = 4 (lane % (D/4)), of the un-normalised result and
+// the sum of weights `l`.
+template <int D, class Ml, class Acc>
+__device__ __forceinline__ f32x4_t combine_pieces(int np, const Ml &ml_of, const Acc &acc_of, int lane, float &l)
+{
+    constexpr int kRowLanes = D / 4, kRows = kWave / kRowLanes;   // rows per load instruction
+    constexpr int kFirst = 4, kMore = 8;                          // loads in flight: with the weights, and after them
+    const int sub = lane / kRowLanes, c4 = 4 * (lane % kRowLanes);
+    auto row = [&](int i) { return *reinterpret_cast<const f32x4_t *>(acc_of(min(i, np - 1)) + c4); };
+    // The weights of up to 64 pieces and the first rows, all loads issued together.
+    const f32x2_t ml0 = *reinterpret_cast<const f32x2_t *>(ml_of(min(lane, np - 1)));
+    f32x4_t first[kFirst];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        x += __shfl_xor(x, off, kWave);
-    return x;
+    for (int k = 0; k < kFirst; ++k)
+        first[k] = row(kRows * k + sub);
+    float M = wave_max(lane < np ? ml0[0] : -__builtin_inff());
+    for (int c0 = kWave; c0 < np; c0 += kWave)   // units spread over more than 64 workers
+        M = fmaxf(M, wave_max(ml_of(min(c0 + lane, np - 1))[0]));
+    // Weights c_i = 2^(m_i - M); a zero weight (underflow, nothing but minus
+    // infinities) drops its row.
+    float c = lane < np ? __builtin_amdgcn_exp2f(ml0[0] - M) : 0.0f;
+    l = wave_sum(c * ml0[1]);
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    auto add = [&](float w, f32x4_t x) {
+        if (w != 0.0f)
+            acc += w * x;
+    };
+#pragma unroll
+    for (int k = 0; k < kFirst; ++k)
+        add(__shfl(c, kRows * k + sub, kWave), first[k]);
+    for (int c0 = 0; c0 < np; c0 += kWave) {
+        if (c0 > 0) {
+            const f32x2_t ml = *reinterpret_cast<const f32x2_t *>(ml_of(min(c0 + lane, np - 1)));
+            c = c0 + lane < np ? __builtin_amdgcn_exp2f(ml[0] - M) : 0.0f;
+            l += wave_sum(c * ml[1]);
+        }
+        const int cnt = min(kWave, np - c0);
+        for (int i = c0 == 0 ? kRows * kFirst : 0; i < cnt; i += kRows * kMore) {
+            f32x4_t x[kMore];
+#pragma unroll
+            for (int k = 0; k < kMore; ++k)
+                x[k] = row(c0 + i + kRows * k + sub);
+#pragma unroll
+            for (int k = 0; k < kMore; ++k) {
+                const int at = i + kRows * k + sub;
+                add(at < kWave ? __shfl(c, at & (kWave - 1), kWave) : 0.0f, x[k]);
+            }
+        }
+    }
+    // The rows of one instruction lie in different lanes: add them up.
+#pragma unroll
+    for (int off = kRowLanes; off < kWave; off <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[e] += __shfl_xor(acc[e], off, kWave);
+    return acc;
+}
+
+__device__ __forceinline__ uint32_t pack2(float a, float b)
+{
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
 // floor(x / y) for 0 <= x < 2^53, 0 < y < 2^31: a double quotient corrected by
@@ -56,8 +148,6 @@ __device__ __forceinline__ long long div_floor(long long x, long long y)
 template <int D, int NEXT>
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p, int merge_blocks)
 {
-    constexpr int E = D / kWave;   // output columns per lane (1 or 2)
-    constexpr int kBatch = 8;      // pieces whose rows are fetched together with the weights
     if constexpr (NEXT != 0) {
         if ((int)blockIdx.x >= merge_blocks) {
             const int ab = (int)blockIdx.x - merge_blocks;
@@ -79,119 +169,42 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p, int
     const int b = u / Hkv;
     const int g = u - b * Hkv;
     const int lane = threadIdx.x & (kWave - 1);
-    uint16_t *dst = p.out + ((size_t)b * p.num_q_heads + (size_t)g * G + j) * D + E * lane;
-    // First round trip: the unit's place in the tile stream.
+    const int c4 = 4 * (lane % (D / 4));   // the lane's columns
+    uint16_t *dst = p.out + ((size_t)b * p.num_q_heads + (size_t)g * G + j) * D + c4;
+    // First round trip: the unit's place in the stream.
     const int cb = p.cum_pages[b];
     const int nb = p.cum_pages[b + 1] - cb;
     const int len = p.seq_lens[b];
     const long long total = (long long)p.cum_pages[p.batch] * Hkv;
 
     if (nb == 0) {
-        const uint16_t fill = len < 0 ? 0x7fc0 : 0x0000;   // bf16 NaN / +0
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            dst[e] = fill;
+        const uint32_t fill = len < 0 ? 0x7fc07fc0u : 0u;   // bf16 NaN / +0
+        if (lane < D / 4)
+            *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{fill, fill};
         return;
     }
     const long long NW = effective_workers(total, p.num_workers, p.step_tiles);
-    const long long a = (long long)Hkv * cb + (long long)g * nb;   // first tile of the unit
-    const long long e = a + nb;                                    // one past its last tile
-    // Worker holding tile x: the largest w with floor(w * total / NW) <= x.
+    const long long a = (long long)Hkv * cb + (long long)g * nb;   // first step of the unit
+    const long long e = a + nb;                                    // one past its last step
+    // Worker holding step x: the largest w with floor(w * total / NW) <= x.
     const int wf = (int)div_floor((a + 1) * NW - 1, total);
     const int wl = (int)div_floor(e * NW - 1, total);
     if (wf == wl)
         return;
     const int np = wl - wf + 1;
-
-    // Piece i (lane i, i < 64) comes from worker wf + i. Its slot is 2w, except
-    // for the unit's first worker when the unit began after that worker's first
-    // tile (then it was the worker's trailing piece, slot 2w + 1). A worker with
-    // an empty range has no piece (slot -1).
-    auto slot_of = [&](int i) -> int {
-        const long long w = wf + i;
-        const long long s = div_floor(w * total, NW);
-        if (s == div_floor((w + 1) * total, NW))
-            return -1;
-        return (int)(2 * w + ((i == 0 && s < a) ? 1 : 0));
-    };
-    // Second round trip: the weights of up to 64 pieces and the rows of the
-    // first kBatch pieces, all loads issued together.
-    const int my_slot = lane < np ? slot_of(lane) : -1;
-    f32x2_t ml = {-__builtin_inff(), 0.0f};
-    if (my_slot >= 0)
-        ml = *reinterpret_cast<const f32x2_t *>(p.part_ml + ((size_t)my_slot * G + j) * 2);
-    float row[kBatch][E];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-        const int si = __builtin_amdgcn_readlane(my_slot, i);
-#pragma unroll
-        for (int k = 0; k < E; ++k)
-            row[i][k] = 0.0f;
-        if (i < np && si >= 0) {
-            const float *src = p.part_acc + ((size_t)si * G + j) * D + E * lane;
-            if constexpr (E == 2) {
-                const f32x2_t v = *reinterpret_cast<const f32x2_t *>(src);
-                row[i][0] = v[0];
-                row[i][1] = v[1];
-            } else {
-                row[i][0] = src[0];
-            }
-        }
-    }
-    float M = wave_max(ml[0]);
-    for (int c0 = kWave; c0 < np; c0 += kWave) {   // units spread over more than 64 workers
-        const int s2 = lane + c0 < np ? slot_of(lane + c0) : -1;
-        M = fmaxf(M, wave_max(s2 >= 0 ? p.part_ml[((size_t)s2 * G + j) * 2] : -__builtin_inff()));
-    }
-    // Weights c_i = 2^(m_i - M); a zero weight (empty worker, underflow) drops its row.
-    float c = my_slot >= 0 ? __builtin_amdgcn_exp2f(ml[0] - M) : 0.0f;
-    float Lsum = wave_sum(c * ml[1]);
-    float acc[E];
-#pragma unroll
-    for (int k = 0; k < E; ++k)
-        acc[k] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-        const float ci = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c), i));
-#pragma unroll
-        for (int k = 0; k < E; ++k)
-            acc[k] += ci != 0.0f ? ci * row[i][k] : 0.0f;
-    }
-    // Pieces past the first kBatch (long units cut across many workers).
-    for (int c0 = 0; c0 < np; c0 += kWave) {
-        int sl = my_slot;
-        float cl = c;
-        if (c0 > 0) {
-            sl = lane + c0 < np ? slot_of(lane + c0) : -1;
-            float ml0 = -__builtin_inff(), ml1 = 0.0f;
-            if (sl >= 0) {
-                const f32x2_t v = *reinterpret_cast<const f32x2_t *>(p.part_ml + ((size_t)sl * G + j) * 2);
-                ml0 = v[0];
-                ml1 = v[1];
-            }
-            cl = sl >= 0 ? __builtin_amdgcn_exp2f(ml0 - M) : 0.0f;
-            Lsum += wave_sum(cl * ml1);
-        }
-        const int lo = c0 == 0 ? kBatch : 0;
-        const int cnt = min(kWave, np - c0);
-        for (int i = lo; i < cnt; ++i) {
-            const float ci = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cl), i));
-            const int si = __builtin_amdgcn_readlane(sl, i);
-            if (ci == 0.0f || si < 0)
-                continue;
-            const float *src = p.part_acc + ((size_t)si * G + j) * D + E * lane;
-#pragma unroll
-            for (int k = 0; k < E; ++k)
-                acc[k] += ci * src[k];
-        }
-    }
-    const float inv = 1.0f / Lsum;
-    if constexpr (E == 2) {
-        const f32x2_t o = {acc[0] * inv, acc[1] * inv};
-        *reinterpret_cast<bf16x2_t *>(dst) = __builtin_convertvector(o, bf16x2_t);
-    } else {
-        *reinterpret_cast<__bf16 *>(dst) = (__bf16)(acc[0] * inv);
-    }
+    // Piece i comes from worker wf + i (no worker's range is empty: NW <=
+    // total). Its slot is 2w, except for the unit's first worker when the unit
+    // began after that worker's first step (then it was the worker's trailing
+    // piece, slot 2w + 1).
+    const int odd = div_floor((long long)wf * total, NW) < a ? 1 : 0;
+    auto row_of = [&](int i) { return (size_t)(2 * (wf + i) + (i == 0 ? odd : 0)) * G + j; };
+    float l;
+    const f32x4_t acc = combine_pieces<D>(
+        np, [&](int i) { return p.part_ml + 2 * row_of(i); }, [&](int i) { return p.part_acc + row_of(i) * D; }, lane, l);
+    const float inv = 1.0f / l;
+    if (lane < D / 4)
+        *reinterpret_cast<u32x2_t *>(dst) =
+            u32x2_t{pack2(acc[0] * inv, acc[1] * inv), pack2(acc[2] * inv, acc[3] * inv)};
 }
 
 // Prefix-sharing mode: every (sequence, head) row with shared pages, or whose
@@ -205,8 +218,6 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p, int
 template <int D>
 __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMergeParams p)
 {
-    constexpr int E = D / kWave;
-    constexpr int kBatch = 8;   // pieces whose rows are fetched together with the weights
     const int Hkv = p.num_kv_heads, G = p.group, Hq = p.num_q_heads;
     const int item = blockIdx.x * (kMergeThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (item >= p.batch * Hq)
@@ -216,7 +227,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
     const int g = h / G;
     const int hl = h - g * G;
     const int lane = threadIdx.x & (kWave - 1);
-    uint16_t *dst = p.out + ((size_t)b * Hq + h) * D + E * lane;
+    const int c4 = 4 * (lane % (D / 4));   // the lane's columns
+    uint16_t *dst = p.out + ((size_t)b * Hq + h) * D + c4;
     // First round trip: the sequence's place in both tile streams.
     const int32_t *info = p.seq_shared + 4 * (size_t)b;   // first shared step, shared pages, lead, shared steps
     const int s_start = info[0], sk = info[1], lead = info[2], ss = info[3];
@@ -227,10 +239,9 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
     const long long tot_s = (long long)p.cum_shared[p.max_sub] * Hkv;
     const bool bad = L < 0 || L > p.max_blocks * kPageSize || L < sk * kPageSize;
     if (sk == 0 && ob == 0) {
-        const uint16_t fill = L < 0 ? 0x7fc0 : 0x0000;   // bf16 NaN / +0
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            dst[e] = fill;
+        const uint32_t fill = L < 0 ? 0x7fc07fc0u : 0u;   // bf16 NaN / +0
+        if (lane < D / 4)
+            *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{fill, fill};
         return;
     }
     const long long nw_o = effective_workers(tot_o, p.num_workers, p.step_tiles);
@@ -257,119 +268,34 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
         row = (b - lead) * G + hl;
     }
     const int np = n_s + n_o;
-    // Piece i: code = shared (bit 31) | unit area (bit 30) | slot << 6 | row, or -1 if
-    // the worker's range is empty. Slots stay below 2^17 (workers) and unit indices
-    // below B Hkv < 2^24, so no code is -1.
-    auto piece = [&](int i) -> int {
-        if (i < n_s) {
-            if (n_s == 1)
-                return (int)(0xC0000000u | ((uint32_t)(lead * Hkv + g) << 6) | (uint32_t)row);
-            const long long w = wf_s + i;
-            const long long s = div_floor(w * tot_s, nw_s);
-            if (s == div_floor((w + 1) * tot_s, nw_s))
-                return -1;
-            const long long slot = 2 * w + ((w == wf_s && s < a_s) ? 1 : 0);
-            return (int)(0x80000000u | (uint32_t)(slot << 6) | (uint32_t)row);
-        }
-        if (n_o == 1)   // sk > 0 here: a whole own unit of an unshared sequence was written out
-            return (int)(0x40000000u | ((uint32_t)(b * Hkv + g) << 6) | (uint32_t)hl);
-        const long long w = wf_o + (i - n_s);
-        const long long s = div_floor(w * tot_o, nw_o);
-        if (s == div_floor((w + 1) * tot_o, nw_o))
-            return -1;
-        const long long slot = 2 * w + ((w == wf_o && s < a_o) ? 1 : 0);
-        return (int)((uint32_t)(slot << 6) | (uint32_t)hl);
+    // Pieces 0 .. n_s - 1 are the shared unit's, the others the own unit's. A
+    // unit in one piece keeps its state in the unit area (an own unit of an
+    // unshared sequence was written out instead: sk > 0 here). Otherwise piece
+    // i of a unit is worker wf + i's, in slot 2w, or 2w + 1 for its first worker
+    // if the unit began after that worker's first step (no worker's range is
+    // empty).
+    const int odd_s = sk > 0 && div_floor(wf_s * tot_s, nw_s) < a_s ? 1 : 0;
+    const int odd_o = ob > 0 && div_floor(wf_o * tot_o, nw_o) < a_o ? 1 : 0;
+    const float *const ml_s = n_s == 1 ? p.shared_unit_ml : p.shared_ml;
+    const float *const acc_s = n_s == 1 ? p.shared_unit_acc : p.shared_acc;
+    const float *const ml_o = n_o == 1 ? p.own_unit_ml : p.own_ml;
+    const float *const acc_o = n_o == 1 ? p.own_unit_acc : p.own_acc;
+    auto row_s = [&](int i) {
+        const size_t slot = n_s == 1 ? (size_t)(lead * Hkv + g) : (size_t)(2 * (wf_s + i) + (i == 0 ? odd_s : 0));
+        return slot * kPrefixRows + row;
     };
-    auto ml_of = [&](int code) -> const float * {
-        const size_t slot = (size_t)((uint32_t)code & 0x3fffffffu) >> 6;
-        const size_t r = (size_t)(code & 63);
-        const bool unit = ((uint32_t)code & 0x40000000u) != 0;
-        if (code < 0)
-            return (unit ? p.shared_unit_ml : p.shared_ml) + (slot * kPrefixRows + r) * 2;
-        return (unit ? p.own_unit_ml : p.own_ml) + (slot * G + r) * 2;
+    auto row_o = [&](int i) {
+        const size_t slot = n_o == 1 ? (size_t)(b * Hkv + g) : (size_t)(2 * (wf_o + i) + (i == 0 ? odd_o : 0));
+        return slot * G + hl;
     };
-    auto acc_of = [&](int code) -> const float * {
-        const size_t slot = (size_t)((uint32_t)code & 0x3fffffffu) >> 6;
-        const size_t r = (size_t)(code & 63);
-        const bool unit = ((uint32_t)code & 0x40000000u) != 0;
-        if (code < 0)
-            return (unit ? p.shared_unit_acc : p.shared_acc) + (slot * kPrefixRows + r) * D;
-        return (unit ? p.own_unit_acc : p.own_acc) + (slot * G + r) * D;
-    };
-    // Second round trip: the weights of up to 64 pieces and the rows of the
-    // first kBatch pieces, all loads issued together.
-    const int my_code = lane < np ? piece(lane) : -1;
-    f32x2_t ml = {-__builtin_inff(), 0.0f};
-    if (my_code != -1)
-        ml = *reinterpret_cast<const f32x2_t *>(ml_of(my_code));
-    float rowv[kBatch][E];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-        const int ci = __builtin_amdgcn_readlane(my_code, i);
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            rowv[i][e] = 0.0f;
-        if (i < np && ci != -1) {
-            const float *src = acc_of(ci) + E * lane;
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                rowv[i][e] = src[e];
-        }
-    }
-    float M = wave_max(ml[0]);
-    for (int c0 = kWave; c0 < np; c0 += kWave) {   // more than 64 pieces
-        const int c2 = lane + c0 < np ? piece(lane + c0) : -1;
-        M = fmaxf(M, wave_max(c2 != -1 ? ml_of(c2)[0] : -__builtin_inff()));
-    }
-    // Weights c_i = 2^(m_i - M); a zero weight (empty worker, underflow) drops its row.
-    const float c = my_code != -1 ? __builtin_amdgcn_exp2f(ml[0] - M) : 0.0f;
-    float Lsum = wave_sum(c * ml[1]);
-    float acc[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-        acc[e] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) {
-        const float ci = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c), i));
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            acc[e] += ci != 0.0f ? ci * rowv[i][e] : 0.0f;
-    }
-    // Pieces past the first kBatch.
-    for (int c0 = 0; c0 < np; c0 += kWave) {
-        int cl = my_code;
-        float wl = c;
-        if (c0 > 0) {
-            cl = lane + c0 < np ? piece(lane + c0) : -1;
-            float m0 = -__builtin_inff(), l0 = 0.0f;
-            if (cl != -1) {
-                const f32x2_t v = *reinterpret_cast<const f32x2_t *>(ml_of(cl));
-                m0 = v[0];
-                l0 = v[1];
-            }
-            wl = cl != -1 ? __builtin_amdgcn_exp2f(m0 - M) : 0.0f;
-            Lsum += wave_sum(wl * l0);
-        }
-        const int lo = c0 == 0 ? kBatch : 0;
-        const int cnt = min(kWave, np - c0);
-        for (int i = lo; i < cnt; ++i) {
-            const float ci = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wl), i));
-            const int ki = __builtin_amdgcn_readlane(cl, i);
-            if (ki == -1 || ci == 0.0f)
-                continue;
-            const float *src = acc_of(ki) + E * lane;
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                acc[e] += ci * src[e];
-        }
-    }
-    const float inv = bad ? __builtin_nanf("") : 1.0f / Lsum;
-    if constexpr (E == 2) {
-        const f32x2_t o = {acc[0] * inv, acc[1] * inv};
-        *reinterpret_cast<bf16x2_t *>(dst) = __builtin_convertvector(o, bf16x2_t);
-    } else {
-        *reinterpret_cast<__bf16 *>(dst) = (__bf16)(acc[0] * inv);
-    }
+    float l;
+    const f32x4_t acc = combine_pieces<D>(
+        np, [&](int i) { return i < n_s ? ml_s + 2 * row_s(i) : ml_o + 2 * row_o(i - n_s); },
+        [&](int i) { return i < n_s ? acc_s + row_s(i) * D : acc_o + row_o(i - n_s) * D; }, lane, l);
+    const float inv = bad ? __builtin_nanf("") : 1.0f / l;
+    if (lane < D / 4)
+        *reinterpret_cast<u32x2_t *>(dst) =
+            u32x2_t{pack2(acc[0] * inv, acc[1] * inv), pack2(acc[2] * inv, acc[3] * inv)};
 }
 
 }  // namespace

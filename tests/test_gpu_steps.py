@@ -1,0 +1,79 @@
+"""Decode attention where its pipeline steps and its merge can go wrong: units whose pages do not
+fill their last step of one, two or four tiles, ranges longer than the 64 steps described at a time,
+units cut into many pieces, and bad pages or scales next to a step's live tiles."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_15930_amd import inputs, sl
+from parity import assert_parity, oracle_full
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs an MI355X")]
+DEV = "cuda:0"
+KINDS = [(64, "bf16"), (128, "bf16"), (64, "e4m3"), (128, "e4m3")]
+
+
+def _say(*a):
+    print(*a, flush=True)
+
+
+@pytest.mark.parametrize("workers", [1, 2, 3, 11])
+@pytest.mark.parametrize("D,kv", KINDS)
+def test_step_and_chunk_edges(D, kv, workers):
+    """1 .. 9 pages with a full, a single and a 15-token last page, and ranges of 63 .. 130 steps."""
+    L = [16 * n + r for n in range(9) for r in (1, 15, 16)] + [16 * 62 + 5, 16 * 129, 16 * 257 + 1]
+    _say("step edges", D, kv, workers)
+    b = inputs.make_paged_batch(L, 6, 2, D, seed=D + workers, device=DEV, kv_dtype=kv)
+    out = sl.run_batch(b, num_workers=workers)
+    torch.cuda.synchronize()
+    assert_parity(out, oracle_full(b), f"D={D} {kv} workers={workers}")
+
+
+@pytest.mark.parametrize("pieces", [2, 8, 9, 16, 17, 33, 64, 65, 129])
+@pytest.mark.parametrize("D,kv", KINDS)
+def test_unit_cut_into_many_pieces(D, kv, pieces):
+    """One KV head over `pieces` workers (a worker takes at least eight tiles): the merge's first
+    batch of rows, the loop after it and the second chunk of 64 weights."""
+    L = [16 * 8 * pieces - 7]
+    _say("pieces", D, kv, pieces)
+    b = inputs.make_paged_batch(L, 7, 1, D, seed=pieces, device=DEV, kv_dtype=kv)
+    out = sl.run_batch(b, num_workers=pieces)
+    torch.cuda.synchronize()
+    assert_parity(out, oracle_full(b), f"D={D} {kv} pieces={pieces}")
+
+
+@pytest.mark.parametrize("page", [0, 1, 2, 3, 4, 6])
+@pytest.mark.parametrize("D,kv", KINDS)
+def test_page_outside_the_pool_at_every_place_of_a_step(D, kv, page):
+    """The sequence that names it gets NaN rows, its neighbours theirs."""
+    L = [100, 16 * 7, 50]
+    _say("bad page", D, kv, page)
+    b = inputs.make_paged_batch(L, 4, 2, D, seed=3, device=DEV, kv_dtype=kv)
+    want = sl.run_batch(b, num_workers=2).clone()
+    b.block_table[1, page] = b.k_pages.shape[0] if page % 2 else -1
+    out = sl.run_batch(b, num_workers=2)
+    torch.cuda.synchronize()
+    assert torch.isnan(out[1].float()).all()
+    assert torch.equal(out[0], want[0]) and torch.equal(out[2], want[2])
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 0.0])
+@pytest.mark.parametrize("D", [64, 128])
+def test_scales_of_pages_not_read_do_not_leak(D, bad):
+    """A step's missing tiles are multiplied by no scale but those of its own pages."""
+    L = [16 * n + 3 for n in range(6)]
+    _say("scales", D, bad)
+    b = inputs.make_paged_batch(L, 4, 2, D, seed=5, device=DEV, kv_dtype="e4m3")
+    # what page 0 holds moves to a new page; page 0 and the poison page then go bad
+    n = b.k_pages.shape[0]
+    b.k_pages, b.v_pages = torch.cat([b.k_pages, b.k_pages[:1]]), torch.cat([b.v_pages, b.v_pages[:1]])
+    b.k_scales, b.v_scales = torch.cat([b.k_scales, b.k_scales[:1]]), torch.cat([b.v_scales, b.v_scales[:1]])
+    b.block_table = torch.where(b.block_table == 0, torch.full_like(b.block_table, n), b.block_table)
+    want = oracle_full(b)
+    for s in (b.k_scales, b.v_scales):
+        s[0] = bad
+        s[b.poison_page] = bad
+    out = sl.run_batch(b, num_workers=3)
+    torch.cuda.synchronize()
+    assert_parity(out, want, f"D={D} bad={bad}")
