@@ -48,11 +48,9 @@ using sl::kPageSize;
 constexpr int kRing = 8;
 constexpr int kRingGroup = 4;
 constexpr int kRingEvents = kRing / kRingGroup;
-// One-launch step: a wave gets at least this many tiles of its unit, and the
-// step takes the one-launch path only while its longest wave range is within
+// One-launch step: taken only while its longest wave range is within
 // kUnitSlackTiles tiles of a split-kernel worker's share (the two-launch
 // step spreads tiles over all workers but pays a second launch).
-constexpr int kUnitMinTiles = 1;
 constexpr int kUnitThreads = sl::kUnitWaves * sl::kWave;
 constexpr int kUnitSlackTiles = 8;
 
@@ -262,19 +260,33 @@ bool sl_engine::plan_unit_step(const Staged &sg)
     }
     if (n == 0 || (long long)n * Hkv > cus)
         return false;
-    // Workgroups per unit: its share of the CUs by tiles, at least one, and
-    // at most enough to give every wave kUnitMinTiles tiles.
-    int blocks = 0, wave_tiles = 0;
-    for (int e = 0; e < n; ++e) {
-        const int nb = (up.len[e] + kPageSize - 1) / kPageSize;
-        long long k = (long long)cus * nb / (tiles * Hkv);
-        const long long kmax = (nb + sl::kUnitWaves * kUnitMinTiles - 1) / (sl::kUnitWaves * kUnitMinTiles);
-        k = std::max(1LL, std::min(std::min(k, kmax), (long long)sl::kMaxUnitSplit));
-        up.first[e] = blocks;
-        blocks += Hkv * (int)k;
-        wave_tiles = std::max(wave_tiles, (int)((nb + sl::kUnitWaves * k - 1) / (sl::kUnitWaves * k)));
+    // Workgroups per unit: the fewest that leave every wave at most wave_tiles
+    // tiles, for the smallest wave_tiles (to a sixteenth) whose workgroups fit
+    // the chip in one pass: the longest wave sets the step's time. (Giving
+    // every unit the whole part of its share of the CUs left some waves with
+    // nearly twice the tiles of others: a 96-sample generation took 33.2
+    // instead of 32.5 ms.)
+    const long long all_waves = (long long)cus * sl::kUnitWaves;
+    int wave_tiles = (int)std::max(1LL, (tiles * Hkv + all_waves - 1) / all_waves);
+    int blocks = 0;
+    for (;; wave_tiles += std::max(1, wave_tiles / 16)) {
+        const int per = sl::kUnitWaves * wave_tiles;
+        bool fits = true;
+        blocks = 0;
+        for (int e = 0; e < n; ++e) {
+            const int nb = (up.len[e] + kPageSize - 1) / kPageSize;
+            const int k = (nb + per - 1) / per, waves = k * sl::kUnitWaves;
+            fits &= k <= sl::kMaxUnitSplit;
+            up.first[e] = blocks;
+            up.split[e] = (uint32_t)(k - 1) | (uint32_t)(nb % waves) << 6 | (uint32_t)(nb / waves) << 16;
+            blocks += Hkv * k;
+        }
+        if (fits && blocks <= cus)
+            break;
     }
     up.first[n] = blocks;
+    if (wave_tiles >= 1 << 16)   // the quotients' field
+        return false;
     const long long worker_tiles = (tiles * Hkv + nw - 1) / nw;
     if (blocks > sl::kMaxUnitBlocks || wave_tiles > worker_tiles + kUnitSlackTiles)
         return false;

@@ -116,12 +116,20 @@ __device__ __forceinline__ f32x2_t load2_device(__amdgpu_buffer_rsrc_t r, int of
 // This lane's part of the argument arrays, fetched before anything else so
 // that it arrives together with the scalar arguments.
 struct UnitArgs {
-    int32_t f_lo, f_hi, seq_lo, seq_hi, len_lo, len_hi;
+    int32_t f_lo, f_hi, seq_lo, seq_hi, len_lo, len_hi, split_lo, split_hi;
 };
 __device__ __forceinline__ UnitArgs unit_args(const UnitStepParams &up, int lane)
 {
-    return UnitArgs{up.first[lane + 1], up.first[lane + 1 + kWave], up.seq[lane],
-                    up.seq[lane + kWave], up.len[lane],             up.len[lane + kWave]};
+    return UnitArgs{up.first[lane + 1],   up.first[lane + 1 + kWave], up.seq[lane],   up.seq[lane + kWave],
+                    up.len[lane],         up.len[lane + kWave],       (int32_t)up.split[lane], (int32_t)up.split[lane + kWave]};
+}
+
+// floor(x / y) for 0 <= x < 2^16, 0 < y < 2^12: (x + 1/2) / y is at least
+// 1 / 2y away from every integer, far more than the reciprocal's error. (An
+// integer division is some 30 dependent instructions, 0.1 us.)
+__device__ __forceinline__ int small_div(int x, int y)
+{
+    return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y));
 }
 
 template <int D, bool FP8>
@@ -144,15 +152,17 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
         return i < kWave ? __builtin_amdgcn_readlane(lo, i & (kWave - 1)) : __builtin_amdgcn_readlane(hi, i & (kWave - 1));
     };
     const int first_e = e > 0 ? pick(ar.f_lo, ar.f_hi, e - 1) : 0;
-    const int K = (pick(ar.f_lo, ar.f_hi, e) - first_e) / Hkv;
+    const uint32_t split = (uint32_t)pick(ar.split_lo, ar.split_hi, e);
+    const int K = (int)(split & 63u) + 1;
     const int local = blk - first_e;
-    const int g = local / K, k = local - g * K;
+    const int g = small_div(local, K), k = local - g * K;
     const int b = pick(ar.seq_lo, ar.seq_hi, e);
     const int L = pick(ar.len_lo, ar.len_hi, e);
     const int max_len = p.max_blocks * kPageSize;
     const int Lc = min(L, max_len);
     const int nb = pages_of(L, max_len);
     const uint32_t row0 = (uint32_t)(b * p.num_q_heads + g * G);
+    const int next_page = FP8 && up.units_append ? up.next_page[e] : -1;   // fetched ahead of the tail that needs it
     if (nb == 0) {   // the host lists sequences of length >= 1 only; defined anyway: zero rows
         if (k == 0)
             for (int i = threadIdx.x; i < G * D / 8; i += kUnitThreads)
@@ -160,12 +170,11 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
         return;
     }
 
-    // This wave's tiles [t0, t0 + nt) of the unit: floor(gw nb / waves) ..
-    // floor((gw + 1) nb / waves), without the wide product.
-    const unsigned waves = (unsigned)K * kUnitWaves, gw = (unsigned)k * kUnitWaves + wave;
-    const unsigned per = (unsigned)nb / waves, rem = (unsigned)nb % waves;
-    const int t0 = (int)(gw * per + gw * rem / waves);
-    const int nt = (int)((gw + 1) * per + (gw + 1) * rem / waves) - t0;
+    // This wave's tiles [t0, t0 + nt) of the unit: the host's quotient and
+    // remainder of nb over the waves, the first waves taking one tile more.
+    const int per = (int)(split >> 16), rem = (int)(split >> 6 & 1023u), gw = k * kUnitWaves + wave;
+    const int t0 = gw * per + min(gw, rem);
+    const int nt = per + (gw < rem ? 1 : 0);
 
     Piece<D> st;
     reset(st);
@@ -246,7 +255,7 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     const __amdgpu_buffer_rsrc_t ml_rsrc = piece_rsrc(p.part_ml, sizeof(float) * kMaxUnitBlocks * mls);
     const __amdgpu_buffer_rsrc_t acc_rsrc = piece_rsrc(p.part_acc, sizeof(float) * kMaxUnitBlocks * G * D);
     for (int item = threadIdx.x; item < G * (D / 4); item += kUnitThreads) {
-        const int cn = item % G, w4 = item / G;              // row; (c, r, quad) of its columns
+        const int w4 = small_div(item, G), cn = item - w4 * G;   // (c, r, quad) of its columns; row
         const int cq = w4 & 3, cr = (w4 >> 2) & 3, c = w4 >> 4;
         const int cl = cn + 16 * cq;                         // source lane
         const float *src = states + (16 * c + cr) * kWave + cl;
@@ -293,10 +302,10 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     // The unit's next-step row, by the last wave: with one workgroup per unit,
     // every wave's reads of the unit's pages are done once the barrier above
     // has passed.
-    const bool tail_append = up.units_append && wave == kUnitWaves - 1;
+    const bool tail_append = FP8 && up.units_append && wave == kUnitWaves - 1;
     if (K == 1) {
         if (tail_append)
-            append_row<D, FP8>(up.next, b * Hkv + g, L + 1, up.next_page[e], lane);
+            append_row<D, FP8>(up.next, b * Hkv + g, L + 1, next_page, lane);
         return;
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -311,7 +320,7 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     // Every workgroup of the unit has counted its arrival after its loads
     // returned, so none reads the unit's pages any more.
     if (tail_append)
-        append_row<D, FP8>(up.next, b * Hkv + g, L + 1, up.next_page[e], lane);
+        append_row<D, FP8>(up.next, b * Hkv + g, L + 1, next_page, lane);
     // The last arrival merges the unit's K pieces (slots first[e] + g K ..),
     // in slot order, row j and four columns per thread. Up to eight pieces:
     // every load at once; more: the (m, l) pairs through LDS first, then

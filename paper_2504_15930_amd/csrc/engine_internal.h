@@ -42,6 +42,8 @@ struct UnitStepParams {
     int32_t len[kMaxUnitEntries];        // its length
     int32_t next_page[kMaxUnitEntries];  // units_append: page of its next token (-1: it finished)
     int32_t first[kMaxUnitEntries + 1];  // its first workgroup; Hkv * K_e workgroups, head-major
+    uint32_t split[kMaxUnitEntries];     // K_e - 1 in bits [5:0]; its tiles over its K_e * kUnitWaves waves: remainder
+                                         // in [15:6], quotient in [31:16]
     int32_t zero[kMaxUnitEntries];       // slots whose output rows are cleared (zero_blocks of them)
 };
 hipError_t launch_unit_step(const UnitStepParams &up, int head_dim, bool fp8, hipStream_t stream);
