@@ -7,7 +7,9 @@ without a GPU tensor every entry point raises.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
+import functools
 import os
 
 import torch
@@ -126,20 +128,51 @@ def num_workers(desc: Desc, fp8: bool = False) -> int:
     return n.value
 
 
+# Host time per call counts: a small step's kernels take less than the calls
+# around them (18.1 us per call of 8 short sequences, 7.6 of them the library's
+# two launches). A device context costs 1.4 us and a Stream object 1.9, so the
+# one is entered only when the tensors' device is not the current one, and the
+# stream is asked for as the raw handle (0.1 us); the workspace sizes of the
+# shapes in use are kept.
+_no_context = contextlib.nullcontext()
+
+
+def _device(index: int):
+    return _no_context if torch.cuda.current_device() == index else torch.cuda.device(index)
+
+
+def _stream(index: int) -> int:
+    """Raw handle of the current stream of GPU ``index``."""
+    return torch._C._cuda_getCurrentRawStream(index)
+
+
+@functools.lru_cache(maxsize=256)
+def _workspace_bytes(index: int, *sizes) -> int:
+    """``workspace_size`` for ``make_desc``'s sizes on GPU ``index`` (current): they decide it alone."""
+    return workspace_size(make_desc(*sizes))
+
+
+@functools.lru_cache(maxsize=256)
+def _prefix_workspace_bytes(index: int, num_groups: int, *sizes) -> int:
+    desc, need = make_desc(*sizes), ctypes.c_size_t(0)
+    _check(load().sl_decode_attn_prefix_workspace_size(ctypes.byref(desc), num_groups, ctypes.byref(need)),
+           "sl_decode_attn_prefix_workspace_size")
+    return need.value
+
+
 _workspaces: dict[tuple[int, int], torch.Tensor] = {}
 
 
-def _workspace(device: torch.device, nbytes: int) -> torch.Tensor:
-    """A cached scratch buffer of at least ``nbytes`` (256-byte aligned by torch) per (device,
+def _workspace(index: int, stream: int, nbytes: int) -> torch.Tensor:
+    """A cached scratch buffer of at least ``nbytes`` (256-byte aligned by torch) per (GPU,
     current stream). Calls on one stream run one after the other, so they may share a buffer;
     calls on two streams could overlap, so each stream gets its own. The buffer is allocated
     while its stream is current, so when it is replaced by a larger one torch's allocator hands
     its memory out again only in that stream's order, after the kernels that used it."""
-    idx = device.index if device.index is not None else torch.cuda.current_device()
-    key = (idx, torch.cuda.current_stream(device).cuda_stream)
+    key = (index, stream)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
-        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=torch.device("cuda", index))
         _workspaces[key] = ws
     return ws
 
@@ -182,13 +215,15 @@ def _run(fp8, q, k_pages, v_pages, k_scales, v_scales, block_table, seq_lens, sc
         _need(out, "out", torch.bfloat16, 3)
         if out.shape != q.shape:
             raise ValueError("out must have the shape of q")
-    with torch.cuda.device(q.device):
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        desc = make_desc(B, Hq, Hkv, D, P, block_table.shape[1], N, num_workers_, stream)
+    index = q.get_device()
+    with _device(index):
+        stream = _stream(index)
+        sizes = (B, Hq, Hkv, D, P, block_table.shape[1], N, num_workers_)
+        desc = make_desc(*sizes, stream)
         if B == 0:
             return out
-        need = workspace_size(desc)
-        ws = workspace if workspace is not None else _workspace(q.device, need)
+        need = _workspace_bytes(index, *sizes)
+        ws = workspace if workspace is not None else _workspace(index, stream, need)
         desc.workspace = ws.data_ptr()
         desc.workspace_bytes = ws.numel() * ws.element_size()
         if timing is not None:
@@ -240,9 +275,9 @@ def decode_attn_noalloc(q, k_pages, v_pages, block_table, seq_lens, scale, *, ou
         _need(out, "out", torch.bfloat16, 3)
         if out.shape != q.shape:
             raise ValueError("out must have the shape of q")
-    with torch.cuda.device(q.device):
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        desc = make_desc(B, Hq, Hkv, D, P, block_table.shape[1], N, num_workers, stream)
+    index = q.get_device()
+    with _device(index):
+        desc = make_desc(B, Hq, Hkv, D, P, block_table.shape[1], N, num_workers, _stream(index))
         _check(load().sl_decode_attn_noalloc(ctypes.byref(desc), q.data_ptr(), k_pages.data_ptr(),
                                              v_pages.data_ptr(), block_table.data_ptr(), seq_lens.data_ptr(),
                                              float(scale), out.data_ptr()),
@@ -294,9 +329,9 @@ def kv_append(k_new, v_new, block_table, seq_lens, k_pages, v_pages, *, k_scales
         raise ValueError("block_table / seq_lens rows must equal the batch")
     if fp8 and (tuple(k_scales.shape) != (N, Hkv) or tuple(v_scales.shape) != (N, Hkv)):
         raise ValueError("scales must have shape [num_pages, num_kv_heads]")
-    with torch.cuda.device(k_new.device):
-        stream = torch.cuda.current_stream(k_new.device).cuda_stream
-        desc = make_desc(B, num_q_heads or Hkv, Hkv, D, P, block_table.shape[1], N, 0, stream)
+    index = k_new.get_device()
+    with _device(index):
+        desc = make_desc(B, num_q_heads or Hkv, Hkv, D, P, block_table.shape[1], N, 0, _stream(index))
         if timing is not None:
             desc.timing_start, desc.timing_stop = timing
         lib = load()
@@ -341,15 +376,15 @@ def _run_prefix(fp8, q, k_pages, v_pages, k_scales, v_scales, block_table, seq_l
         if out.shape != q.shape:
             raise ValueError("out must have the shape of q")
     lib = load()
-    with torch.cuda.device(q.device):
-        stream = torch.cuda.current_stream(q.device).cuda_stream
-        desc = make_desc(B, Hq, Hkv, D, P, block_table.shape[1], N, num_workers, stream)
+    index = q.get_device()
+    with _device(index):
+        stream = _stream(index)
+        sizes = (B, Hq, Hkv, D, P, block_table.shape[1], N, num_workers)
+        desc = make_desc(*sizes, stream)
         if B == 0:
             return out
-        need = ctypes.c_size_t(0)
-        _check(lib.sl_decode_attn_prefix_workspace_size(ctypes.byref(desc), ng, ctypes.byref(need)),
-               "sl_decode_attn_prefix_workspace_size")
-        ws = workspace if workspace is not None else _workspace(q.device, need.value)
+        need = _prefix_workspace_bytes(index, ng, *sizes)
+        ws = workspace if workspace is not None else _workspace(index, stream, need)
         desc.workspace = ws.data_ptr()
         desc.workspace_bytes = ws.numel() * ws.element_size()
         if timing is not None:
