@@ -170,6 +170,18 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
         return;
     }
 
+    // The unit's next-step rows (E4M3), K by the first half of the waves and V
+    // by the second: what they need (it is complete since the last launch) is
+    // fetched here by every workgroup of the unit, ahead of the stream, and
+    // written once all of the unit's reads are done, these included.
+    static_assert(kUnitWaves == 8, "four wavefronts each append K and V");
+    const bool tail_append = FP8 && up.units_append && append_valid(up.next, L + 1, next_page);
+    AppendE4m3<D> app;
+    if (tail_append) {
+        app.load_row(up.next, b * Hkv + g, wave / 4, lane);
+        app.load_tile(up.next, g, wave / 4, next_page, wave % 4, lane);
+    }
+
     // This wave's tiles [t0, t0 + nt) of the unit: the host's quotient and
     // remainder of nb over the waves, the first waves taking one tile more.
     const int per = (int)(split >> 16), rem = (int)(split >> 6 & 1023u), gw = k * kUnitWaves + wave;
@@ -242,6 +254,11 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
         dst[(D / 4) * kWave] = st.m;
         dst[(D / 4 + 1) * kWave] = lsum;
     }
+    if (tail_append) {   // (a wave without tiles has not waited for its loads yet)
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    }
     const bool bad_any = __syncthreads_or(bad ? 1 : 0) != 0;
     const float poison = bad_any ? __builtin_nanf("") : 0.0f;
 
@@ -299,13 +316,9 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
                 store2_device(ml_rsrc, 4 * (blk * mls + 2 * cn), f32x2_t{M + poison, l});
         }
     }
-    // The unit's next-step row, by the last wave: with one workgroup per unit,
-    // every wave's reads of the unit's pages are done once the barrier above
-    // has passed.
-    const bool tail_append = FP8 && up.units_append && wave == kUnitWaves - 1;
     if (K == 1) {
-        if (tail_append)
-            append_row<D, FP8>(up.next, b * Hkv + g, L + 1, next_page, lane);
+        if (tail_append)   // the only workgroup: its waves have loaded since the barrier above
+            app.store(L + 1, wave % 4, lane);
         return;
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -320,7 +333,7 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     // Every workgroup of the unit has counted its arrival after its loads
     // returned, so none reads the unit's pages any more.
     if (tail_append)
-        append_row<D, FP8>(up.next, b * Hkv + g, L + 1, next_page, lane);
+        app.store(L + 1, wave % 4, lane);
     // The last arrival merges the unit's K pieces (slots first[e] + g K ..),
     // in slot order, row j and four columns per thread. Up to eight pieces:
     // every load at once; more: the (m, l) pairs through LDS first, then
@@ -420,7 +433,7 @@ __global__ __launch_bounds__(kUnitThreads) void engine_unit_step_kernel(UnitStep
         return;
     const int unit = blk * kUnitWaves + (int)(threadIdx.x / kWave);
     if (unit < up.next.batch * up.next.num_kv_heads)
-        append_unit<D, FP8>(up.next, unit, threadIdx.x & (kWave - 1));
+        append_unit_bf16<D>(up.next, unit, threadIdx.x & (kWave - 1));
 }
 
 }  // namespace

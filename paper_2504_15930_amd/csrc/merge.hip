@@ -32,39 +32,6 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-// One step of a wave reduction: the value of the lane that the DPP control
-// names, or `none` where there is no such lane or its row is masked out.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float lane_from(float x, float none)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none),
-                                                                 __builtin_bit_cast(int, x), CTRL, ROWS, 0xf, false));
-}
-// Reductions over the wavefront, the result in every lane: shifts by 1, 2, 4
-// and 8 within rows of 16 lanes, then the row totals passed on (a vector
-// instruction each, where a shuffle is a round trip through LDS).
-__device__ __forceinline__ float wave_max(float x)
-{
-    constexpr float kNone = -__builtin_inff();
-    x = fmaxf(x, lane_from<0x111, 0xf>(x, kNone));
-    x = fmaxf(x, lane_from<0x112, 0xf>(x, kNone));
-    x = fmaxf(x, lane_from<0x114, 0xf>(x, kNone));
-    x = fmaxf(x, lane_from<0x118, 0xf>(x, kNone));
-    x = fmaxf(x, lane_from<0x142, 0xa>(x, kNone));
-    x = fmaxf(x, lane_from<0x143, 0xc>(x, kNone));
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), kWave - 1));
-}
-__device__ __forceinline__ float wave_sum(float x)
-{
-    x += lane_from<0x111, 0xf>(x, 0.0f);
-    x += lane_from<0x112, 0xf>(x, 0.0f);
-    x += lane_from<0x114, 0xf>(x, 0.0f);
-    x += lane_from<0x118, 0xf>(x, 0.0f);
-    x += lane_from<0x142, 0xa>(x, 0.0f);
-    x += lane_from<0x143, 0xc>(x, 0.0f);
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), kWave - 1));
-}
-
 // Combine the np >= 1 pieces of one row: ml_of(i) and acc_of(i) give the
 // addresses of piece i's (m, l) pair and of its D accumulators. Every lane
 // gets four columns, c4 = 4 (lane % (D/4)), of the un-normalised result and
@@ -152,9 +119,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p, int
         if ((int)blockIdx.x >= merge_blocks) {
             const int ab = (int)blockIdx.x - merge_blocks;
             apply_stage(p.next, ab * kMergeThreads + threadIdx.x, ((int)gridDim.x - merge_blocks) * kMergeThreads);
-            const int unit = ab * (kMergeThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-            if (unit < p.next.batch * p.next.num_kv_heads)
-                append_unit<D, NEXT == 2>(p.next, unit, threadIdx.x & (kWave - 1));
+            append_block<D, NEXT == 2>(p.next, ab);
             return;
         }
     }
@@ -305,8 +270,12 @@ hipError_t launch_merge(const MergeParams &p, int head_dim, hipStream_t stream)
     const long long items = (long long)p.batch * p.num_kv_heads * p.group;
     const int per_block = kMergeThreads / kWave;
     const int merge_blocks = (int)((items + per_block - 1) / per_block);
-    const int next_blocks =
-        p.next_kind != 0 ? (int)(((long long)p.next.batch * p.next.num_kv_heads + per_block - 1) / per_block) : 0;
+    static_assert(kMergeThreads == kAppendThreads, "the append's workgroups ride in the merge's launch");
+    int next_blocks = 0;
+    if (p.next_kind != 0) {
+        const long long units = (long long)p.next.batch * p.next.num_kv_heads;
+        next_blocks = (int)(p.next_kind == 2 ? append_blocks<true>(units) : append_blocks<false>(units));
+    }
     const dim3 grid((unsigned)(merge_blocks + next_blocks));
     const dim3 block(kMergeThreads);
 #define SL_MERGE(DD, NN) hipLaunchKernelGGL((merge_kernel<DD, NN>), grid, block, 0, stream, p, merge_blocks)

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2504_15930_amd import inputs, sl
 from parity import assert_parity, oracle_full
 
@@ -77,3 +78,31 @@ def test_scales_of_pages_not_read_do_not_leak(D, bad):
     out = sl.run_batch(b, num_workers=3)
     torch.cuda.synchronize()
     assert_parity(out, want, f"D={D} bad={bad}")
+
+
+@pytest.mark.parametrize("grow", ["none", "all", "some"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_e4m3_append_at_every_slot(D, grow):
+    """A tile is re-encoded by four wavefronts of four rows each: every slot, with scales that stay,
+    grow, or grow in some heads, equals the oracle byte for byte; a fresh page ignores its old scale."""
+    rng = np.random.default_rng(D)
+    Hkv, lens = 3, np.arange(1, 34, dtype=np.int32)
+    B, N = len(lens), 3 * len(lens)
+    bt = rng.permutation(N).astype(np.int32).reshape(B, 3)
+    gain = {"none": 1e-3, "all": 50.0, "some": np.array([1e-3, 50.0, 1.0])[None, :, None]}[grow]
+
+    def row():
+        x = torch.from_numpy((rng.standard_normal((B, Hkv, D)) * gain).astype(np.float32)).to(torch.bfloat16)
+        return x, x.view(torch.int16).numpy().view(np.uint16)
+
+    (k, kbits), (v, vbits) = row(), row()
+    pages = [rng.integers(0, 0x7E, (N, Hkv, 16, D)).astype(np.uint8) for _ in range(2)]
+    scales = [rng.uniform(0.01, 0.1, (N, Hkv)).astype(np.float32) for _ in range(2)]
+    want = oracle.kv_append(kbits, vbits, bt, lens, *pages, k_scales=scales[0], v_scales=scales[1])
+    got = [torch.from_numpy(a.copy()).to(DEV) for a in pages + scales]
+    _say("append slots", D, grow)
+    sl.kv_append(k.to(DEV), v.to(DEV), torch.from_numpy(bt).to(DEV), torch.from_numpy(lens).to(DEV), got[0], got[1],
+                 k_scales=got[2], v_scales=got[3])
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        assert np.array_equal(g.cpu().numpy().view(np.uint8), np.ascontiguousarray(w).view(np.uint8))
