@@ -8,7 +8,7 @@
 //     out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i
 // in fp32, rounded to bf16.
 //
-// One wavefront per (unit, query head). Lane i first fetches (m_i, l_i) of
+// One wavefront per (sequence, query head). Lane i first fetches (m_i, l_i) of
 // piece i, so the maximum, the weights c_i = 2^(m_i - M) and their weighted
 // sum come out of two wave reductions instead of a serial walk. The rows are
 // read as four columns per lane, D/4 lanes per row and so 256/D rows per load
@@ -47,8 +47,8 @@ __device__ __forceinline__ f32x4_t combine_pieces(int np, const Ml &ml_of, const
     const f32x2_t ml0 = *reinterpret_cast<const f32x2_t *>(ml_of(min(lane, np - 1)));
     f32x4_t first[kFirst];
 #pragma unroll
-    for (int k = 0; k < kFirst; ++k)
-        first[k] = row(kRows * k + sub);
+    for (int k = 0; k < kFirst; ++k)   // (k > 0: most units are cut in two or three)
+        first[k] = k == 0 || np > kRows * k ? row(kRows * k + sub) : f32x4_t{0.f, 0.f, 0.f, 0.f};
     float M = wave_max(lane < np ? ml0[0] : -__builtin_inff());
     for (int c0 = kWave; c0 < np; c0 += kWave)   // units spread over more than 64 workers
         M = fmaxf(M, wave_max(ml_of(min(c0 + lane, np - 1))[0]));
@@ -98,44 +98,86 @@ __device__ __forceinline__ uint32_t pack2(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-// floor(x / y) for 0 <= x < 2^53, 0 < y < 2^31: a double quotient corrected by
-// one step (64-bit integer division is a long software sequence on the GPU).
-__device__ __forceinline__ long long div_floor(long long x, long long y)
+// floor(x / y) per lane, for whole 0 <= x < 2^52 and 0 < y < 2^31 and a
+// quotient below 2^31. The reciprocal is good to some 2^-52 after two Newton
+// steps, so the product's floor is off by one at most, which the remainder
+// (exact: every term is below 2^53) shows.
+__device__ __forceinline__ int floor_div(double x, double y)
 {
-    long long q = (long long)((double)x / (double)y);
-    if (q * y > x)
-        --q;
-    else if ((q + 1) * y <= x)
-        ++q;
-    return q;
+    double r = __builtin_amdgcn_rcp(y);
+    r = __builtin_fma(r, __builtin_fma(-y, r, 1.0), r);
+    r = __builtin_fma(r, __builtin_fma(-y, r, 1.0), r);
+    const int q = (int)(x * r);
+    const double rem = __builtin_fma(-(double)q, y, x);
+    return rem < 0.0 ? q - 1 : rem >= y ? q + 1 : q;
+}
+
+// Where a unit's steps [a, a + n) (n >= 1) lie in a stream of `total` steps
+// over nw workers: its first worker, how many it was cut over, and whether it
+// began after the first one's first step (worker w's is floor(w total / nw),
+// and floor(z) < a is z < a).
+struct Cut {
+    int first, pieces, odd;
+};
+// Of two streams at once, one division for all four ends: the lanes of a
+// wavefront divide side by side. (A double quotient with its conversions is
+// some hundred instructions, and with 28 wavefronts on a CU that all work one
+// out, instructions set the time: with three or six of them per row the rows'
+// first loads came back 2.4 (plain) and 4.4 us (prefix) into the kernel in the
+// middle, 0.7 when alone.)
+struct Cuts {
+    Cut s, o;
+};
+__device__ __forceinline__ Cuts cuts_of(long long a_s, int n_s, long long tot_s, int nw_s, long long a_o, int n_o,
+                                        long long tot_o, int nw_o, int lane)
+{
+    // Worker holding step x: the largest w with floor(w total / nw) <= x, which
+    // is floor(((x + 1) nw - 1) / total).
+    const bool own = (lane & 2) != 0;
+    const long long end = (own ? a_o : a_s) + ((lane & 1) != 0 ? (own ? n_o : n_s) : 1);
+    const double nw = own ? nw_o : nw_s, tot = __builtin_fmax((double)(own ? tot_o : tot_s), 1.0);
+    const int w = floor_div(__builtin_fma((double)end, nw, -1.0), tot);
+    Cuts c;
+    c.s.first = __builtin_amdgcn_readlane(w, 0);
+    c.s.pieces = __builtin_amdgcn_readlane(w, 1) - c.s.first + 1;
+    c.s.odd = c.s.first * tot_s < a_s * nw_s ? 1 : 0;
+    c.o.first = __builtin_amdgcn_readlane(w, 2);
+    c.o.pieces = __builtin_amdgcn_readlane(w, 3) - c.o.first + 1;
+    c.o.odd = c.o.first * tot_o < a_o * nw_o ? 1 : 0;
+    return c;
+}
+
+// Head h's KV head, h / group (group_inverse: the host's ceil(2^32 / group)).
+__device__ __forceinline__ int kv_head(int h, int group, uint32_t group_inverse)
+{
+    return group == 1 ? h : (int)(((uint64_t)(uint32_t)h * group_inverse) >> 32);
 }
 
 // NEXT: the decode engine's next-step append in the same launch (0 none,
 // 1 bf16 cache, 2 E4M3 cache), in the workgroups after the merge's.
 template <int D, int NEXT>
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p, int merge_blocks)
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p)
 {
+    const int b = blockIdx.y;   // rows of workgroups: one per sequence, then the append's
     if constexpr (NEXT != 0) {
-        if ((int)blockIdx.x >= merge_blocks) {
-            const int ab = (int)blockIdx.x - merge_blocks;
-            apply_stage(p.next, ab * kMergeThreads + threadIdx.x, ((int)gridDim.x - merge_blocks) * kMergeThreads);
+        if (b >= p.batch) {
+            const int ab = (b - p.batch) * (int)gridDim.x + (int)blockIdx.x;
+            apply_stage(p.next, ab * kMergeThreads + threadIdx.x,
+                        ((int)gridDim.y - p.batch) * (int)gridDim.x * kMergeThreads);
             append_block<D, NEXT == 2>(p.next, ab);
             return;
         }
     }
     const int Hkv = p.num_kv_heads;
     const int G = p.group;
-    const int item = blockIdx.x * (kMergeThreads / kWave) +
-                     __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    if (item >= p.batch * Hkv * G)
+    const int h = blockIdx.x * (kMergeThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (h >= p.num_q_heads)
         return;
-    const int u = item / G;
-    const int j = item - u * G;
-    const int b = u / Hkv;
-    const int g = u - b * Hkv;
+    const int g = kv_head(h, G, p.group_inverse);
+    const int j = h - g * G;
     const int lane = threadIdx.x & (kWave - 1);
     const int c4 = 4 * (lane % (D / 4));   // the lane's columns
-    uint16_t *dst = p.out + ((size_t)b * p.num_q_heads + (size_t)g * G + j) * D + c4;
+    uint16_t *dst = p.out + ((size_t)b * p.num_q_heads + h) * D + c4;
     // First round trip: the unit's place in the stream.
     const int cb = p.cum_pages[b];
     const int nb = p.cum_pages[b + 1] - cb;
@@ -148,24 +190,20 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p, int
             *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{fill, fill};
         return;
     }
-    const long long NW = effective_workers(total, p.num_workers, p.step_tiles);
+    const int NW = effective_workers(total, p.num_workers, p.step_tiles);
     const long long a = (long long)Hkv * cb + (long long)g * nb;   // first step of the unit
-    const long long e = a + nb;                                    // one past its last step
-    // Worker holding step x: the largest w with floor(w * total / NW) <= x.
-    const int wf = (int)div_floor((a + 1) * NW - 1, total);
-    const int wl = (int)div_floor(e * NW - 1, total);
-    if (wf == wl)
+    const Cut cut = cuts_of(a, nb, total, NW, a, nb, total, NW, lane).s;
+    if (cut.pieces == 1)
         return;
-    const int np = wl - wf + 1;
-    // Piece i comes from worker wf + i (no worker's range is empty: NW <=
+    // Piece i comes from worker first + i (no worker's range is empty: NW <=
     // total). Its slot is 2w, except for the unit's first worker when the unit
     // began after that worker's first step (then it was the worker's trailing
     // piece, slot 2w + 1).
-    const int odd = div_floor((long long)wf * total, NW) < a ? 1 : 0;
-    auto row_of = [&](int i) { return (size_t)(2 * (wf + i) + (i == 0 ? odd : 0)) * G + j; };
+    auto row_of = [&](int i) { return (size_t)(2 * (cut.first + i) + (i == 0 ? cut.odd : 0)) * G + j; };
     float l;
     const f32x4_t acc = combine_pieces<D>(
-        np, [&](int i) { return p.part_ml + 2 * row_of(i); }, [&](int i) { return p.part_acc + row_of(i) * D; }, lane, l);
+        cut.pieces, [&](int i) { return p.part_ml + 2 * row_of(i); },
+        [&](int i) { return p.part_acc + row_of(i) * D; }, lane, l);
     const float inv = 1.0f / l;
     if (lane < D / 4)
         *reinterpret_cast<u32x2_t *>(dst) =
@@ -184,12 +222,11 @@ template <int D>
 __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMergeParams p)
 {
     const int Hkv = p.num_kv_heads, G = p.group, Hq = p.num_q_heads;
-    const int item = blockIdx.x * (kMergeThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    if (item >= p.batch * Hq)
+    const int b = blockIdx.y;
+    const int h = blockIdx.x * (kMergeThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (h >= Hq)
         return;
-    const int b = item / Hq;
-    const int h = item - b * Hq;
-    const int g = h / G;
+    const int g = kv_head(h, G, p.group_inverse);
     const int hl = h - g * G;
     const int lane = threadIdx.x & (kWave - 1);
     const int c4 = 4 * (lane % (D / 4));   // the lane's columns
@@ -209,38 +246,26 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
             *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{fill, fill};
         return;
     }
-    const long long nw_o = effective_workers(tot_o, p.num_workers, p.step_tiles);
+    const int nw_o = effective_workers(tot_o, p.num_workers, p.step_tiles);
+    const int nw_s = effective_workers(tot_s,
+                                       effective_shared_workers(tot_o, p.num_workers, p.num_shared_workers,
+                                                                p.max_shared_workers, p.step_tiles),
+                                       p.step_tiles);
     const long long a_o = (long long)Hkv * co + (long long)g * ob;
-    int wf_o = 0, n_o = 0;
-    if (ob > 0) {
-        wf_o = (int)div_floor((a_o + 1) * nw_o - 1, tot_o);
-        n_o = (int)div_floor((a_o + ob) * nw_o - 1, tot_o) - wf_o + 1;
-    }
+    const long long a_s = (long long)Hkv * s_start + (long long)g * ss;
+    const Cuts cuts = cuts_of(a_s, ss, tot_s, nw_s, a_o, ob, tot_o, nw_o, lane);   // (an empty unit's is not used)
+    const int wf_o = cuts.o.first, odd_o = cuts.o.odd, n_o = ob > 0 ? cuts.o.pieces : 0;
+    const int wf_s = cuts.s.first, odd_s = cuts.s.odd, n_s = sk > 0 ? cuts.s.pieces : 0;
     if (sk == 0 && n_o == 1)
         return;   // finished by a single worker
-    const long long nw_s =
-        tot_s > 0 ? effective_workers(tot_s,
-                                      effective_shared_workers(tot_o, p.num_workers, p.num_shared_workers,
-                                                               p.max_shared_workers, p.step_tiles),
-                                      p.step_tiles)
-                  : 1;
-    long long a_s = 0;
-    int wf_s = 0, n_s = 0, row = 0;
-    if (sk > 0) {
-        a_s = (long long)Hkv * s_start + (long long)g * ss;
-        wf_s = (int)div_floor((a_s + 1) * nw_s - 1, tot_s);
-        n_s = (int)div_floor((a_s + ss) * nw_s - 1, tot_s) - wf_s + 1;
-        row = (b - lead) * G + hl;
-    }
+    const int row = (b - lead) * G + hl;
     const int np = n_s + n_o;
     // Pieces 0 .. n_s - 1 are the shared unit's, the others the own unit's. A
     // unit in one piece keeps its state in the unit area (an own unit of an
     // unshared sequence was written out instead: sk > 0 here). Otherwise piece
-    // i of a unit is worker wf + i's, in slot 2w, or 2w + 1 for its first worker
-    // if the unit began after that worker's first step (no worker's range is
-    // empty).
-    const int odd_s = sk > 0 && div_floor(wf_s * tot_s, nw_s) < a_s ? 1 : 0;
-    const int odd_o = ob > 0 && div_floor(wf_o * tot_o, nw_o) < a_o ? 1 : 0;
+    // i of a unit is worker first + i's, in slot 2w, or 2w + 1 for its first
+    // worker if the unit began after that worker's first step (no worker's
+    // range is empty).
     const float *const ml_s = n_s == 1 ? p.shared_unit_ml : p.shared_ml;
     const float *const acc_s = n_s == 1 ? p.shared_unit_acc : p.shared_acc;
     const float *const ml_o = n_o == 1 ? p.own_unit_ml : p.own_ml;
@@ -267,18 +292,17 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
 
 hipError_t launch_merge(const MergeParams &p, int head_dim, hipStream_t stream)
 {
-    const long long items = (long long)p.batch * p.num_kv_heads * p.group;
     const int per_block = kMergeThreads / kWave;
-    const int merge_blocks = (int)((items + per_block - 1) / per_block);
     static_assert(kMergeThreads == kAppendThreads, "the append's workgroups ride in the merge's launch");
-    int next_blocks = 0;
+    long long next_blocks = 0;
     if (p.next_kind != 0) {
         const long long units = (long long)p.next.batch * p.next.num_kv_heads;
-        next_blocks = (int)(p.next_kind == 2 ? append_blocks<true>(units) : append_blocks<false>(units));
+        next_blocks = p.next_kind == 2 ? append_blocks<true>(units) : append_blocks<false>(units);
     }
-    const dim3 grid((unsigned)(merge_blocks + next_blocks));
+    const unsigned x = (unsigned)((p.num_q_heads + per_block - 1) / per_block);
+    const dim3 grid(x, (unsigned)(p.batch + (next_blocks + x - 1) / x));
     const dim3 block(kMergeThreads);
-#define SL_MERGE(DD, NN) hipLaunchKernelGGL((merge_kernel<DD, NN>), grid, block, 0, stream, p, merge_blocks)
+#define SL_MERGE(DD, NN) hipLaunchKernelGGL((merge_kernel<DD, NN>), grid, block, 0, stream, p)
     if (head_dim == 128 && p.next_kind == 0)
         SL_MERGE(128, 0);
     else if (head_dim == 128 && p.next_kind == 1)
@@ -297,15 +321,10 @@ hipError_t launch_merge(const MergeParams &p, int head_dim, hipStream_t stream)
     return hipGetLastError();
 }
 
-}  // namespace sl
-
-namespace sl {
-
 hipError_t launch_merge_prefix(const PrefixMergeParams &p, int head_dim, hipStream_t stream)
 {
-    const long long items = (long long)p.batch * p.num_q_heads;
     const int per_block = kMergeThreads / kWave;
-    const dim3 grid((unsigned)((items + per_block - 1) / per_block));
+    const dim3 grid((unsigned)((p.num_q_heads + per_block - 1) / per_block), (unsigned)p.batch);
     if (head_dim == 128)
         hipLaunchKernelGGL(merge_prefix_kernel<128>, grid, dim3(kMergeThreads), 0, stream, p);
     else if (head_dim == 64)

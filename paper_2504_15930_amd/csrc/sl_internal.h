@@ -79,6 +79,10 @@ __host__ __device__ inline int effective_shared_workers(long long own_total, int
 }
 constexpr size_t kAlign = 256;
 
+// ceil(2^32 / group) (2^32 itself, for a group of 1, does not fit): h / group
+// is the high half of h times this, exact for h group < 2^32.
+inline uint32_t inverse_of(int group) { return (uint32_t)(((1ull << 32) + (unsigned)group - 1) / (unsigned)group); }
+
 // Step metadata, one word per step of a stream:
 //   [4] last step of its unit, [5] first step of its unit, [6] the sequence
 //   length is invalid or the block table named a page outside the pool,
@@ -179,6 +183,7 @@ struct PrefixMergeParams {
     int32_t num_shared_workers;   // base and largest count of shared-page workgroups
     int32_t max_shared_workers;   // (effective_shared_workers)
     int32_t step_tiles;           // as the split kernel's
+    uint32_t group_inverse;       // ceil(2^32 / group), for heads below 2^28 (unused for a group of 1)
 };
 
 struct AppendParams {
@@ -211,6 +216,7 @@ struct MergeParams {
     uint16_t *out;
     int32_t batch, num_q_heads, num_kv_heads, group, num_workers;
     int32_t step_tiles;   // as the split kernel's
+    uint32_t group_inverse;   // as PrefixMergeParams'
     // Decode engine: the next step's staged append (and its bookkeeping) runs
     // in the same launch, in workgroups after the merge's; 0 none, 1 bf16
     // cache, 2 E4M3 cache. The merge never reads what it writes: it reads the
