@@ -74,6 +74,12 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
     int32_t *const s_prev_end = s_len;   // [NG + 1]: largest end of the earlier groups
     int32_t *const s_base = s_own;       // [NG + 1]: first sub-group of each group
     int32_t *const s_group = s_shared;   // [B + 1]: marks of the groups' first members
+    // The lengths, needed last, come with the group arrays: one trip to memory.
+    constexpr int kPer = (kMaxPrefixBatch + T - 1) / T;
+    int32_t len[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r)
+        len[r] = tid + r * T < B ? p.seq_lens[tid + r * T] : 0;
     // 1. Each group's earlier ends; every sequence starts unmarked. With
     //    group_start ascending (the usual case) the largest earlier end of
     //    group k is its own start, and the scan is skipped.
@@ -102,14 +108,14 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
         const int lo = gs[k], hi = gs[k + 1], sp = s_sp[k];
         const bool ok = lo >= 0 && hi <= B && hi > lo && (ascending || lo >= s_prev_end[k]) && sp > 0 &&
                         sp <= p.max_blocks;
-        s_base[k] = ok ? (hi - lo + M - 1) / M : 0;
+        s_base[k] = ok ? small_div(hi - lo + M - 1, M) : 0;
         if (ok)
             s_group[lo] = k;
     }
     __syncthreads();
     // s_base: first sub-group of each group; s_group[b + 1]: the latest mark at or before b.
     block_exclusive_scan2<ScanSum, ScanMax>(s_base, NG, s_group, B);
-    // 3. The sub-groups: shared pages and packed first member and size.
+    // 3. The sub-groups: shared steps and packed first member and size.
     const int NS = s_base[NG];
     for (int sg = tid; sg < S; sg += T) {
         int sp = 0, gl = 0;
@@ -123,34 +129,37 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
                     khi = mid;
             }
             const int lo = gs[klo], m = gs[klo + 1] - lo;
-            const int ns = (m + M - 1) / M, cm = (m + ns - 1) / ns;
+            const int ns = small_div(m + M - 1, M), cm = small_div(m + ns - 1, ns);
             const int slo = lo + (sg - s_base[klo]) * cm;
             sp = s_sp[klo];
             gl = slo | (min(cm, lo + m - slo) - 1) << 16 | (NT - 1 - (sp + NT - 1) % NT) << 24;
         }
-        s_sh[sg] = sp;
+        s_sh[sg] = (sp + NT - 1) / NT;
         s_gl[sg] = gl;
     }
     // 4. The sub-group of every sequence: the group of the latest mark at or
     //    before b (the exclusive scan's entry b + 1; entry B holds the
-    //    maximum), if b lies inside that group's range.
-    constexpr int kPer = (kMaxPrefixBatch + T - 1) / T;
-    int32_t sub[kPer];
+    //    maximum), if b lies inside that group's range; its shared pages.
+    int32_t sub[kPer], sh[kPer];
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
         const int b = tid + r * T;
         sub[r] = -1;
+        sh[r] = 0;
         if (b < B) {
             const int k = s_group[b + 1];
             if (k >= 0 && b < gs[k + 1]) {
                 const int lo = gs[k], m = gs[k + 1] - lo;
-                const int ns = (m + M - 1) / M, cm = (m + ns - 1) / ns;
-                const int sg = s_base[k] + (b - lo) / cm;
-                sub[r] = sg < S ? sg : -1;   // always below S (prefix_max_sub bounds the count)
+                const int ns = small_div(m + M - 1, M), cm = small_div(m + ns - 1, ns);
+                const int sg = s_base[k] + small_div(b - lo, cm);
+                if (sg < S) {   // always (prefix_max_sub bounds the count)
+                    sub[r] = sg;
+                    sh[r] = s_sp[k];
+                }
             }
         }
     }
-    __syncthreads();
+    __syncthreads();   // the scratch arrays are free
     // 5. Lengths, shared pages and own steps (over the pages after the
     //    sub-group's shared ones).
     const int max_len = p.max_blocks * kPageSize;
@@ -158,17 +167,12 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
     for (int r = 0; r < kPer; ++r) {
         const int b = tid + r * T;
         if (b < B) {
-            const int L = p.seq_lens[b];
-            const int n = pages_of(L, max_len);
-            const int sh = sub[r] >= 0 ? s_sh[sub[r]] : 0;
-            s_len[b] = L;
-            s_shared[b] = sh;
-            s_own[b] = n > sh ? (n - sh + NT - 1) / NT : 0;
+            const int n = pages_of(len[r], max_len);
+            s_len[b] = len[r];
+            s_shared[b] = sh[r];
+            s_own[b] = n > sh[r] ? (n - sh[r] + NT - 1) / NT : 0;
         }
     }
-    __syncthreads();
-    for (int sg = tid; sg < S; sg += T)
-        s_sh[sg] = (s_sh[sg] + NT - 1) / NT;
     __syncthreads();
     block_exclusive_scan2<ScanSum, ScanSum>(s_own, B, s_sh, S);
     if (blockIdx.x == 0) {

@@ -42,6 +42,7 @@
 // scale multiplies the fp32 scores and the value scale multiplies the
 // probabilities before they are rounded for the value MFMA.
 #include "sl_internal.h"
+#include "wave_ops.h"
 
 namespace sl {
 namespace {
@@ -683,6 +684,50 @@ __device__ __forceinline__ void flush_states(const SplitParams &p, int head_dim,
     }
 }
 
+// One array's part of a workgroup scan: the thread's contiguous run of a[0, n)
+// and, after wave(), its exclusive prefix within the wavefront. (DPP scans: as
+// shuffles, each of the six steps is a round trip through LDS.)
+template <class Op>
+struct RunScan {
+    int32_t *a;
+    int lo, hi, excl;
+
+    // The run's place and the wavefront's scan; lane 63 leaves the wavefront's total in *total.
+    __device__ __forceinline__ void wave(int32_t *arr, int n, int32_t *total)
+    {
+        constexpr int T = kWave * kWavesPerBlock;
+        const int tid = threadIdx.x, per = (n + T - 1) / T;
+        a = arr;
+        lo = min(n, tid * per);
+        hi = min(n, lo + per);
+        int local = Op::kIdentity;
+        for (int i = lo; i < hi; ++i)
+            local = Op::op(local, a[i]);
+        const int incl = wave_scan<Op>(local);
+        excl = lane_from<0x138, 0xf>(incl, Op::kIdentity);   // the lane before's
+        if ((tid & (kWave - 1)) == kWave - 1)
+            *total = incl;
+    }
+    // Writes the run's exclusive prefixes; returns the total of all wavefronts.
+    __device__ __forceinline__ int finish(const int32_t *totals) const
+    {
+        const int wave = threadIdx.x / kWave;
+        int run = excl, total = Op::kIdentity;
+#pragma unroll
+        for (int k = 0; k < kWavesPerBlock; ++k) {
+            if (k < wave)
+                run = Op::op(run, totals[k]);
+            total = Op::op(total, totals[k]);
+        }
+        for (int i = lo; i < hi; ++i) {
+            const int v = a[i];
+            a[i] = run;
+            run = Op::op(run, v);
+        }
+        return total;
+    }
+};
+
 // Turns a[0, n) (in LDS, written before a barrier) into its exclusive
 // prefix scan under Op (sum or maximum) and stores the total in a[n]. Every
 // thread of the workgroup calls it; each scans a contiguous run. Ends with a
@@ -691,39 +736,11 @@ template <class Op = ScanSum>
 __device__ __forceinline__ void block_exclusive_scan(int32_t *a, int n)
 {
     __shared__ int32_t s_wave[kWavesPerBlock];
-    constexpr int T = kWave * kWavesPerBlock;
-    const int tid = threadIdx.x;
-    const int per = (n + T - 1) / T;
-    const int lo = min(n, tid * per), hi = min(n, lo + per);
-    int local = Op::kIdentity;
-    for (int i = lo; i < hi; ++i)
-        local = Op::op(local, a[i]);
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
-    int incl = local;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int v = __shfl_up(incl, off, kWave);
-        if (lane >= off)
-            incl = Op::op(incl, v);
-    }
-    const int excl_in_wave = __shfl_up(incl, 1, kWave);
-    if (lane == kWave - 1)
-        s_wave[wave] = incl;
+    RunScan<Op> sa;
+    sa.wave(a, n, s_wave + threadIdx.x / kWave);
     __syncthreads();
-    int base = Op::kIdentity, total = Op::kIdentity;
-#pragma unroll
-    for (int k = 0; k < kWavesPerBlock; ++k) {
-        if (k < wave)
-            base = Op::op(base, s_wave[k]);
-        total = Op::op(total, s_wave[k]);
-    }
-    int run = Op::op(base, lane > 0 ? excl_in_wave : Op::kIdentity);
-    for (int i = lo; i < hi; ++i) {
-        const int v = a[i];
-        a[i] = run;
-        run = Op::op(run, v);
-    }
-    if (tid == 0)
+    const int total = sa.finish(s_wave);
+    if (threadIdx.x == 0)
         a[n] = total;
     __syncthreads();
 }
@@ -734,60 +751,25 @@ template <class OpA, class OpB>
 __device__ __forceinline__ void block_exclusive_scan2(int32_t *a, int n, int32_t *b, int m)
 {
     __shared__ int32_t s_wave[2][kWavesPerBlock];
-    constexpr int T = kWave * kWavesPerBlock;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
-    const int pa = (n + T - 1) / T, pb = (m + T - 1) / T;
-    const int alo = min(n, tid * pa), ahi = min(n, alo + pa);
-    const int blo = min(m, tid * pb), bhi = min(m, blo + pb);
-    int la = OpA::kIdentity, lb = OpB::kIdentity;
-    for (int i = alo; i < ahi; ++i)
-        la = OpA::op(la, a[i]);
-    for (int i = blo; i < bhi; ++i)
-        lb = OpB::op(lb, b[i]);
-    int ia = la, ib = lb;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int va = __shfl_up(ia, off, kWave);
-        const int vb = __shfl_up(ib, off, kWave);
-        if (lane >= off) {
-            ia = OpA::op(ia, va);
-            ib = OpB::op(ib, vb);
-        }
-    }
-    const int ea = __shfl_up(ia, 1, kWave), eb = __shfl_up(ib, 1, kWave);
-    if (lane == kWave - 1) {
-        s_wave[0][wave] = ia;
-        s_wave[1][wave] = ib;
-    }
+    RunScan<OpA> sa;
+    RunScan<OpB> sb;
+    sa.wave(a, n, s_wave[0] + threadIdx.x / kWave);
+    sb.wave(b, m, s_wave[1] + threadIdx.x / kWave);
     __syncthreads();
-    int base_a = OpA::kIdentity, tot_a = OpA::kIdentity, base_b = OpB::kIdentity, tot_b = OpB::kIdentity;
-#pragma unroll
-    for (int k = 0; k < kWavesPerBlock; ++k) {
-        if (k < wave) {
-            base_a = OpA::op(base_a, s_wave[0][k]);
-            base_b = OpB::op(base_b, s_wave[1][k]);
-        }
-        tot_a = OpA::op(tot_a, s_wave[0][k]);
-        tot_b = OpB::op(tot_b, s_wave[1][k]);
-    }
-    int ra = OpA::op(base_a, lane > 0 ? ea : OpA::kIdentity);
-    for (int i = alo; i < ahi; ++i) {
-        const int v = a[i];
-        a[i] = ra;
-        ra = OpA::op(ra, v);
-    }
-    int rb = OpB::op(base_b, lane > 0 ? eb : OpB::kIdentity);
-    for (int i = blo; i < bhi; ++i) {
-        const int v = b[i];
-        b[i] = rb;
-        rb = OpB::op(rb, v);
-    }
-    if (tid == 0) {
+    const int tot_a = sa.finish(s_wave[0]), tot_b = sb.finish(s_wave[1]);
+    if (threadIdx.x == 0) {
         a[n] = tot_a;
         b[m] = tot_b;
     }
     __syncthreads();
+}
+
+// floor(x / y) for 0 <= x < 2^16, 0 < y < 2^13: (x + 1/2) / y is at least
+// 1 / 2y away from every integer, far more than the reciprocal's error. (An
+// integer division is some 30 dependent instructions, 0.1 us.)
+__device__ __forceinline__ int small_div(int x, int y)
+{
+    return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y));
 }
 
 // Pages of a sequence of length L: ceil(clamp(L, 0, max_len) / 16).
@@ -971,8 +953,6 @@ __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, c
     int cpos = 0, cnext = kChunk;   // lane of the next step to issue; first step of the chunk in `ahead`
     Desc ahead = find(0);
     settle(ahead);
-    if (nsteps > kChunk)
-        ahead = find(kChunk);
     auto issue = [&](Step<D, FP8, NT> &x, int i, bool with_q) {   // step i of the range, from lane cpos
         int32_t T[NT];
 #pragma unroll
@@ -988,6 +968,9 @@ __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, c
 #pragma unroll
     for (int k = 0; k < kNbuf - 1; ++k)
         issue(buf[k], k, k == 0);
+    // (after the first loads: the search takes about as long as they do)
+    if (nsteps > kChunk)
+        ahead = find(kChunk);
 
     Piece<D> st;
     reset(st);

@@ -124,14 +124,6 @@ __device__ __forceinline__ UnitArgs unit_args(const UnitStepParams &up, int lane
                     up.len[lane],         up.len[lane + kWave],       (int32_t)up.split[lane], (int32_t)up.split[lane + kWave]};
 }
 
-// floor(x / y) for 0 <= x < 2^16, 0 < y < 2^12: (x + 1/2) / y is at least
-// 1 / 2y away from every integer, far more than the reciprocal's error. (An
-// integer division is some 30 dependent instructions, 0.1 us.)
-__device__ __forceinline__ int small_div(int x, int y)
-{
-    return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y));
-}
-
 template <int D, bool FP8>
 __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const UnitArgs &ar, int blk, uint8_t *smem,
                                                int32_t *s_last)
