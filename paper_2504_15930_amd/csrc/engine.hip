@@ -124,9 +124,14 @@ __device__ __forceinline__ UnitArgs unit_args(const UnitStepParams &up, int lane
                     up.len[lane],         up.len[lane + kWave],       (int32_t)up.split[lane], (int32_t)up.split[lane + kWave]};
 }
 
+struct UnitFlags {
+    int32_t bad[kUnitWaves];   // per wave: an invalid length, or a page outside the pool
+    int32_t last;              // this workgroup is its unit's last to arrive
+};
+
 template <int D, bool FP8>
 __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const UnitArgs &ar, int blk, uint8_t *smem,
-                                               int32_t *s_last)
+                                               UnitFlags *flags)
 {
     const SplitParams &p = up.cur;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -232,33 +237,47 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     }
 
     // Every wave leaves its state in its own LDS area (past the regroup
-    // stages, so nothing needs to wait for them), then one barrier.
-    constexpr int SF = unit_state_floats<D>();
-    float *const states = reinterpret_cast<float *>(smem + unit_stage_bytes<D>());
+    // stages, so nothing needs to wait for them), then one barrier: per lane
+    // D/16 groups of four columns (group 4 c + r: r D/16 + 4 c + 0..3 of the
+    // lane's quarter of a row), then (m, l). Lanes without a query row hold
+    // nothing.
+    f32x4_t *const state_acc = reinterpret_cast<f32x4_t *>(smem + unit_stage_bytes<D>());   // [wave][D/16][lane]
+    f32x2_t *const state_ml = reinterpret_cast<f32x2_t *>(state_acc + kUnitWaves * (D / 16) * kWave);   // [wave][lane]
     {
         const float lsum = quad_sum(st.l);
-        float *dst = states + (size_t)wave * SF * kWave + lane;
+        if (n < G) {
+            f32x4_t *dst = state_acc + wave * (D / 16) * kWave + lane;
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i)
+            for (int c = 0; c < D / 64; ++c)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                dst[(4 * i + r) * kWave] = st.acc[i][r];
-        dst[(D / 4) * kWave] = st.m;
-        dst[(D / 4 + 1) * kWave] = lsum;
+                for (int r = 0; r < 4; ++r)
+                    dst[(4 * c + r) * kWave] = f32x4_t{st.acc[4 * c][r], st.acc[4 * c + 1][r], st.acc[4 * c + 2][r],
+                                                       st.acc[4 * c + 3][r]};
+            state_ml[wave * kWave + lane] = f32x2_t{st.m, lsum};
+        }
     }
     if (tail_append) {   // (a wave without tiles has not waited for its loads yet)
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_s_waitcnt(0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
     }
-    const bool bad_any = __syncthreads_or(bad ? 1 : 0) != 0;
+    // (The library's barrier with a vote costs two barriers more and a load of
+    // the launch's hidden arguments.)
+    if (lane == 0)
+        flags->bad[wave] = bad ? 1 : 0;
+    __syncthreads();
+    int32_t any = 0;
+#pragma unroll
+    for (int w = 0; w < kUnitWaves; ++w)
+        any |= flags->bad[w];
+    const bool bad_any = any != 0;
     const float poison = bad_any ? __builtin_nanf("") : 0.0f;
 
     // Combine the kUnitWaves states, in wave order (so the result does not
-    // depend on timing). An item is four consecutive columns of one row: lane
-    // (n, quad)'s accumulator values 4 i + r for i = 4 c .. 4 c + 3 are the
-    // columns quad D/4 + r D/16 + 4 c + 0..3 of row n. Consecutive threads
-    // take consecutive rows, whose values lie in consecutive banks.
+    // depend on timing). An item is one group of four columns of one row;
+    // consecutive threads take consecutive rows. (As single floats, 34 stores
+    // per lane and 48 loads per item, and with the library's vote and arguments
+    // fetched one by one, the mean step of a generation took 0.6 us longer.)
     const int unit = e * Hkv + g;
     const int mls = unit_ml_stride(G);
     const __amdgpu_buffer_rsrc_t ml_rsrc = piece_rsrc(p.part_ml, sizeof(float) * kMaxUnitBlocks * mls);
@@ -267,15 +286,14 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
         const int w4 = small_div(item, G), cn = item - w4 * G;   // (c, r, quad) of its columns; row
         const int cq = w4 & 3, cr = (w4 >> 2) & 3, c = w4 >> 4;
         const int cl = cn + 16 * cq;                         // source lane
-        const float *src = states + (16 * c + cr) * kWave + cl;
-        float m[kUnitWaves], ls[kUnitWaves], x[kUnitWaves][4];
+        float m[kUnitWaves], ls[kUnitWaves];
+        f32x4_t x[kUnitWaves];
 #pragma unroll
         for (int w = 0; w < kUnitWaves; ++w) {
-            m[w] = states[((size_t)w * SF + D / 4) * kWave + cl];
-            ls[w] = states[((size_t)w * SF + D / 4 + 1) * kWave + cl];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                x[w][i] = src[((size_t)w * SF + 4 * i) * kWave];
+            const f32x2_t ml = state_ml[w * kWave + cl];
+            m[w] = ml[0];
+            ls[w] = ml[1];
+            x[w] = state_acc[(w * (D / 16) + 4 * c + cr) * kWave + cl];
         }
         float M = m[0];
 #pragma unroll
@@ -287,7 +305,7 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
         for (int w = 0; w < kUnitWaves; ++w) {
             const float wt = m[w] == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(m[w] - M);
             l += wt * ls[w];
-            a += wt * f32x4_t{x[w][0], x[w][1], x[w][2], x[w][3]};
+            a += wt * x[w];
         }
         const int col = cq * (D / 4) + cr * (D / 16) + 4 * c;
         if (K == 1) {   // the whole unit: normalise and write the columns
@@ -318,9 +336,9 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __syncthreads();
     if (threadIdx.x == 0)
-        *s_last = __hip_atomic_fetch_add(up.counters + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == K - 1;
+        flags->last = __hip_atomic_fetch_add(up.counters + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == K - 1;
     __syncthreads();
-    if (*s_last == 0)
+    if (flags->last == 0)
         return;
     // Every workgroup of the unit has counted its arrival after its loads
     // returned, so none reads the unit's pages any more.
@@ -330,7 +348,7 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     // in slot order, row j and four columns per thread. Up to eight pieces:
     // every load at once; more: the (m, l) pairs through LDS first, then
     // eight pieces' columns at a time.
-    const int slot0 = up.first[e] + g * K;
+    const int slot0 = first_e + g * K;
     if (K <= 8) {
         for (int idx = threadIdx.x; idx < G * (D / 4); idx += kUnitThreads) {
             const int j = idx / (D / 4), c = (idx - j * (D / 4)) * 4;
@@ -405,11 +423,18 @@ template <int D, bool FP8>
 __global__ __launch_bounds__(kUnitThreads) void engine_unit_step_kernel(UnitStepParams up)
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[unit_smem_bytes<D>()];
-    __shared__ int32_t s_last;
+    __shared__ UnitFlags flags;
     const UnitArgs ar = unit_args(up, threadIdx.x & (kWave - 1));
+    // Scalar arguments are loaded where they are first used, and the first touch
+    // of each 64-byte line of them is a trip to memory (a launch's arguments are
+    // in no cache), several in a row on the way to the first tile. Naming a field
+    // of every line has them come with the arrays, in one trip.
+    asm volatile("" ::"s"(up.cur.q), "s"(up.cur.batch), "s"(up.cur.num_pages), "s"(up.next.num_pages), "s"(up.n_entries),
+                 "s"(up.next_blocks), "v"(ar.f_lo), "v"(ar.f_hi), "v"(ar.seq_lo), "v"(ar.seq_hi), "v"(ar.len_lo),
+                 "v"(ar.len_hi), "v"(ar.split_lo), "v"(ar.split_hi));
     int blk = (int)blockIdx.x;
     if (blk < up.unit_blocks) {
-        unit_attention<D, FP8>(up, ar, blk, smem, &s_last);
+        unit_attention<D, FP8>(up, ar, blk, smem, &flags);
         return;
     }
     blk -= up.unit_blocks;
