@@ -328,3 +328,26 @@ def test_engine_rows_that_change_every_step(kv):
     ulp = torch.exp2(torch.floor(torch.log2(mag)) - 7)
     err = (a - b).abs()
     assert not (err > ulp + 1e-5 * mag.clamp_min(1.0)).any(), f"max |diff| {float(err.max()):.3g}"
+
+
+@pytest.mark.parametrize("pages", [[1, 3], [9, 2, 40], [64, 65], [129, 7, 200], [700]])
+@pytest.mark.parametrize("kv,Hq,Hkv,D", [("bf16", 7, 1, 128), ("e4m3", 6, 2, 64)])
+def test_engine_units_in_one_some_and_many_workgroups(kv, Hq, Hkv, D, pages):
+    """Few samples on many CUs: units that one workgroup takes, that at most eight share, and longer
+    ones, with the split chosen by the longest. One launch per step against split + merge, within the
+    two paths' rounding of weights and outputs (as above)."""
+    prompt = np.array([16 * n - 5 for n in pages], np.int32)
+    out = np.full(len(pages), 8, np.int32)
+    got, vmax = {}, 2.0
+    for two in (False, True):
+        print("units in workgroups", kv, pages, two, flush=True)
+        eng = E.Engine(prompt, out, out, batch_slots=len(pages), num_q_heads=Hq, num_kv_heads=Hkv, head_dim=D,
+                       kv_fp8=kv == "e4m3", seed=2, two_launch=two, history_steps=8)
+        vmax = max(vmax, float(eng.v_new.float().abs().max()))
+        assert eng.run() == 8
+        torch.cuda.synchronize()
+        got[two] = eng.history.float().cpu()
+        eng.close()
+    a, b = got[False], got[True]
+    ulp = torch.exp2(torch.floor(torch.log2(torch.maximum(a.abs(), b.abs()).clamp_min(2.0 ** -126))) - 7)
+    assert torch.isfinite(a).all() and ((a - b).abs() <= 2 * ulp + 2.0 ** -7 * vmax).all()
