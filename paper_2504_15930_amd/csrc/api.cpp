@@ -236,6 +236,7 @@ sl_status run(const sl_attn_desc *d, const uint16_t *q, const void *k_pages, con
     mp.num_workers = nw;
     mp.step_tiles = split_step_tiles(d->head_dim, fp8);
     mp.group_inverse = inverse_of(G);
+    mp.fp8 = fp8;
     mp.next_kind = 0;
     if (next) {
         mp.next = *next;
@@ -411,6 +412,7 @@ sl_status run_prefix(const sl_attn_desc *d, const uint16_t *q, const void *k_pag
     mp.max_blocks = d->max_blocks_per_seq;
     mp.step_tiles = split_step_tiles(d->head_dim, fp8);
     mp.group_inverse = inverse_of(G);
+    mp.fp8 = fp8;
     if (launch_merge_prefix(mp, d->head_dim, d->stream) != hipSuccess)
         return SL_ERR_HIP;
     return SL_OK;

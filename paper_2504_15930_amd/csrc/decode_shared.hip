@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void prefix_split_kernel(Sp
     else {
         SplitParams sh = shared;
         sh.num_workers = effective_shared_workers((long long)s_own[B] * own.num_kv_heads, own.num_workers,
-                                                  shared.num_workers, max_shared, NT);
+                                                  shared.num_workers, max_shared, NT, FP8);
         split_unit_worker<D, FP8, kSharedPages>(sh, (int)blockIdx.x - own_blocks,
                                                   StreamLds{s_sh, nullptr, nullptr, s_gl, S},
                                                   __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));

@@ -846,7 +846,7 @@ __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, c
     constexpr int NT = step_tiles<D, FP8>();
     const int Hkv = p.num_kv_heads;
     const long long total = (long long)sv.cum[nseq] * Hkv;
-    const int nw = effective_workers(total, p.num_workers, NT);
+    const int nw = effective_workers(total, p.num_workers, NT, kShared ? 0 : wide_from(p.num_workers, FP8));
     if (w >= nw)
         return;
     const int s0 = __builtin_amdgcn_readfirstlane((int)((long long)w * total / nw));

@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p)
             *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{fill, fill};
         return;
     }
-    const int NW = effective_workers(total, p.num_workers, p.step_tiles);
+    const int NW = effective_workers(total, p.num_workers, p.step_tiles, wide_from(p.num_workers, p.fp8 != 0));
     const long long a = (long long)Hkv * cb + (long long)g * nb;   // first step of the unit
     const Cut cut = cuts_of(a, nb, total, NW, a, nb, total, NW, lane).s;
     if (cut.pieces == 1)
@@ -246,11 +246,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_prefix_kernel(PrefixMerge
             *reinterpret_cast<u32x2_t *>(dst) = u32x2_t{fill, fill};
         return;
     }
-    const int nw_o = effective_workers(tot_o, p.num_workers, p.step_tiles);
+    const int nw_o = effective_workers(tot_o, p.num_workers, p.step_tiles, wide_from(p.num_workers, p.fp8 != 0));
     const int nw_s = effective_workers(tot_s,
                                        effective_shared_workers(tot_o, p.num_workers, p.num_shared_workers,
-                                                                p.max_shared_workers, p.step_tiles),
-                                       p.step_tiles);
+                                                                p.max_shared_workers, p.step_tiles, p.fp8 != 0),
+                                       p.step_tiles, 0);
     const long long a_o = (long long)Hkv * co + (long long)g * ob;
     const long long a_s = (long long)Hkv * s_start + (long long)g * ss;
     const Cuts cuts = cuts_of(a_s, ss, tot_s, nw_s, a_o, ob, tot_o, nw_o, lane);   // (an empty unit's is not used)

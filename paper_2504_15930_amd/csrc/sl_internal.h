@@ -45,22 +45,39 @@ constexpr int kMaxGroup = 16;              // query heads per KV head (one MFMA 
 constexpr int kMaxBatch = 8192;            // the split kernel keeps two ints per sequence in LDS
 constexpr int kMergeThreads = 256;         // one wave per unit, four units per block
 constexpr int kMaxWorkers = 1 << 16;       // keeps partial-state offsets below 2^31 bytes
-#ifndef SL_MIN_TILES_PER_WORKER
-#define SL_MIN_TILES_PER_WORKER 8
-#endif
 // A worker is given at least this many tiles: a small stream (a small batch, a
 // short context) is split over fewer workers rather than cut into pieces of
 // one or two tiles, each of which would cost a partial state and a merge step.
-constexpr int kMinTilesPerWorker = SL_MIN_TILES_PER_WORKER;
+// Calls with eight -> four tiles (MI355X, kernels and the gap between them):
+//   8 sequences of 1..256 tokens, D = 64        10.2 -> 8.2 us
+//   one sequence of 512, 28/4 heads              9.9 -> 8.4
+//   64 of 1..200, 28/4 heads                    15.5 -> 12.2
+//   256 of 1..120, 28/4 heads                   20.2 -> 18.5
+//   3 prompts x 22 samples of ~23 own tokens    25.0 -> 21.5
+// With two, 8 prompts x 8 samples of ~60 own tokens took 26.5 instead of 21.7.
+constexpr int kMinTiles = 4;
+// E4M3: a tile is half as long, and a piece costs as much, so beyond half of
+// the workers it takes this many (64 of 1..200 tokens, below it, 12.6 -> 10.4
+// us with four; 256 of 1..120, beyond it, 14.4 -> 15.4). The shared units of
+// prefix sharing, whose pieces have kPrefixRows rows, take this many always
+// (with four, 3 prompts x 16 samples, 12 heads, D = 64, 26.7 -> 28.6).
+constexpr int kMinTilesWide = 8;
 
 // Workers that take part in a stream of `total` steps of step_tiles tiles (the
 // others exit at once); both the split kernel and the merge derive it from the
-// same total.
-__host__ __device__ inline int effective_workers(long long total, int num_workers, int step_tiles)
+// same total (below 2^28 tiles). `wide`: kMinTilesWide beyond this many workers.
+__host__ __device__ inline int effective_workers(long long total, int num_workers, int step_tiles, int wide)
 {
-    const long long want = (total * step_tiles + kMinTilesPerWorker - 1) / kMinTilesPerWorker;
-    return want < 1 ? 1 : (want < num_workers ? (int)want : num_workers);
+    const int tiles = (int)total * step_tiles;
+    const int few = (tiles + kMinTilesWide - 1) / kMinTilesWide;
+    int want = (tiles + kMinTiles - 1) / kMinTiles;
+    want = want < wide ? want : wide;
+    want = want > few ? want : few;
+    return want < 1 ? 1 : (want < num_workers ? want : num_workers);
 }
+// `wide` for plain attention's stream and the own pages of prefix sharing; the
+// shared pages' is 0.
+__host__ __device__ inline int wide_from(int num_workers, bool fp8) { return fp8 ? num_workers / 2 : num_workers; }
 // Prefix sharing: shared-page workgroups that take part in a call. The launch
 // holds the own-page workgroups and up to twice `base` shared ones, and a CU
 // holds two such workgroups; own-page workgroups without work exit at once,
@@ -68,11 +85,14 @@ __host__ __device__ inline int effective_workers(long long total, int num_worker
 // few own pages still streams its shared pages with two workgroups per CU.
 // The split kernel and the merge derive it from the same totals (own tiles).
 __host__ __device__ inline int effective_shared_workers(long long own_total, int own_workers, int base,
-                                                        int max_workers, int step_tiles)
+                                                        int max_workers, int step_tiles, bool fp8)
 {
     const int own_blocks = (own_workers + kWavesPerBlock - 1) / kWavesPerBlock;
     const int active =
-        own_total > 0 ? (effective_workers(own_total, own_workers, step_tiles) + kWavesPerBlock - 1) / kWavesPerBlock : 0;
+        own_total > 0
+            ? (effective_workers(own_total, own_workers, step_tiles, wide_from(own_workers, fp8)) + kWavesPerBlock - 1) /
+                  kWavesPerBlock
+            : 0;
     const int idle = own_blocks - active;
     const int n = base + (idle < base ? idle : base);
     return n < max_workers ? n : max_workers;
@@ -183,6 +203,7 @@ struct PrefixMergeParams {
     int32_t num_shared_workers;   // base and largest count of shared-page workgroups
     int32_t max_shared_workers;   // (effective_shared_workers)
     int32_t step_tiles;           // as the split kernel's
+    int32_t fp8;
     uint32_t group_inverse;       // ceil(2^32 / group), for heads below 2^28 (unused for a group of 1)
 };
 
@@ -216,6 +237,7 @@ struct MergeParams {
     uint16_t *out;
     int32_t batch, num_q_heads, num_kv_heads, group, num_workers;
     int32_t step_tiles;   // as the split kernel's
+    int32_t fp8;
     uint32_t group_inverse;   // as PrefixMergeParams'
     // Decode engine: the next step's staged append (and its bookkeeping) runs
     // in the same launch, in workgroups after the merge's; 0 none, 1 bf16

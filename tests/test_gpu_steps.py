@@ -106,3 +106,27 @@ def test_e4m3_append_at_every_slot(D, grow):
     torch.cuda.synchronize()
     for g, w in zip(got, want):
         assert np.array_equal(g.cpu().numpy().view(np.uint8), np.ascontiguousarray(w).view(np.uint8))
+
+
+@pytest.mark.parametrize("tiles", [3, 4, 5, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 130])
+@pytest.mark.parametrize("D,kv", KINDS)
+def test_worker_counts_of_small_streams(D, kv, tiles):
+    """The split kernel and the merge each work out how many of the workers take part: around every
+    line of that rule (four tiles per worker, for E4M3 up to half of the workers, eight beyond it),
+    with units that share workers, and with shared pages."""
+    lens = [16 * (tiles // 3), 16 * (tiles - 2 * (tiles // 3)) - 3, 16 * (tiles // 3) - 9]
+    b = inputs.make_paged_batch(lens, 6, 2, D, seed=tiles, device=DEV, kv_dtype=kv)
+    for workers in (1, 8, 9):
+        _say("worker counts", D, kv, tiles, workers)
+        assert_parity(sl.run_batch(b, num_workers=workers), oracle_full(b), f"{kv} tiles={tiles} workers={workers}")
+    b, starts, shared = inputs.make_grpo_batch(3, 2, 16 * (tiles // 3) + 1, seed=tiles, device=DEV, num_q_heads=6,
+                                               num_kv_heads=2, head_dim=D, gen_median=20.0, gen_cap=60, kv_dtype=kv)
+    for workers in (8, 9):
+        if kv == "e4m3":
+            out = sl.decode_attn_prefix_fp8(b.q, b.k_pages, b.v_pages, b.k_scales, b.v_scales, b.block_table,
+                                            b.seq_lens, b.scale, starts, shared, num_workers=workers)
+        else:
+            out = sl.decode_attn_prefix(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens, b.scale, starts, shared,
+                                        num_workers=workers)
+        torch.cuda.synchronize()
+        assert_parity(out, oracle_full(b), f"prefix {kv} tiles={tiles} workers={workers}")
