@@ -20,6 +20,7 @@
 //   softmax running max / sum per head j, kept in the lanes of column j: the
 //           only cross-lane step is a max over the four quads of a column
 //   values  O^T[d][j] += sum_t V[t][d] P[j][t]       v_mfma_f32_16x16x16bf16_1k
+//           (two tiles of a step at once: v_mfma_f32_16x16x32_bf16)
 //           A = V^T (lane (n, quad) holds V[4 quad + r][d_i(n)] for r = 0..3,
 //                    gathered from four 16-byte row loads and repacked)
 //           B = P^T exactly as the score MFMA left it (no data movement)
