@@ -9,9 +9,11 @@ namespace {
 template <int D, bool FP8>
 __global__ __launch_bounds__(kAppendThreads) void append_kernel(AppendParams p)
 {
-    if (p.stage)   // nothing in this launch reads the lengths or the block table from memory in this mode
-        apply_stage(p, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
-    append_block<D, FP8>(p, blockIdx.x);
+    const int blk = blockIdx.x * gridDim.y + blockIdx.y;
+    // Nothing in this launch reads the lengths or the block table from memory in this mode.
+    if (p.stage)
+        apply_stage<kAppendThreads>(p, blk, gridDim.x * gridDim.y);
+    append_block<D, FP8>(p, blk);
 }
 
 }  // namespace
@@ -19,7 +21,10 @@ __global__ __launch_bounds__(kAppendThreads) void append_kernel(AppendParams p)
 hipError_t launch_append(const AppendParams &p, int head_dim, bool fp8, hipStream_t stream)
 {
     const long long units = (long long)p.batch * p.num_kv_heads;
-    const dim3 grid((unsigned)(fp8 ? append_blocks<true>(units) : append_blocks<false>(units)));
+    // E4M3's two workgroups per unit lie along y: a dimension holds fewer than
+    // 2^32 threads, and there are fewer than 2^24 units.
+    const unsigned y = fp8 ? 2 : 1;
+    const dim3 grid((unsigned)((fp8 ? append_blocks<true>(units) : append_blocks<false>(units)) / y), y);
     const dim3 block(kAppendThreads);
     if (head_dim == 128 && !fp8)
         hipLaunchKernelGGL((append_kernel<128, false>), grid, block, 0, stream, p);

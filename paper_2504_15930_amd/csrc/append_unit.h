@@ -163,12 +163,21 @@ struct AppendTile {
     }
 };
 
+constexpr int kMaxApplyBlocks = 4096;
+
 // The engine's bookkeeping for a step (staged mode only): store the step's
-// lengths in set_seq_lens and apply its block-table updates, spread over
-// threads [first, first + nthreads) of the launch. Indices were checked by
-// the engine.
-__device__ __forceinline__ void apply_stage(const AppendParams &p, int first, int nthreads)
+// lengths in set_seq_lens and apply its block-table updates, spread over the
+// first of the launch's `blocks` workgroups (THREADS threads each), of which
+// this one is `blk`: enough of them for any step, and few enough that a thread's
+// index fits 32 bits. Indices were checked by the engine.
+template <int THREADS>
+__device__ __forceinline__ void apply_stage(const AppendParams &p, int blk, int blocks)
 {
+    blocks = min(blocks, kMaxApplyBlocks);
+    if (blk >= blocks)
+        return;
+    const int nthreads = blocks * THREADS;
+    const int first = blk * THREADS + (int)threadIdx.x;
     for (int i = first; i < p.batch; i += nthreads)
         p.set_seq_lens[i] = p.stage[i];
     for (int i = first; i < p.n_upd; i += nthreads) {

@@ -445,7 +445,7 @@ __global__ __launch_bounds__(kUnitThreads) void engine_unit_step_kernel(UnitStep
         return;
     }
     blk -= up.zero_blocks;
-    apply_stage(up.next, blk * kUnitThreads + (int)threadIdx.x, up.next_blocks * kUnitThreads);
+    apply_stage<kUnitWaves * kWave>(up.next, blk, up.next_blocks);
     if (up.units_append)
         return;
     const int unit = blk * kUnitWaves + (int)(threadIdx.x / kWave);

@@ -162,8 +162,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p)
     if constexpr (NEXT != 0) {
         if (b >= p.batch) {
             const int ab = (b - p.batch) * (int)gridDim.x + (int)blockIdx.x;
-            apply_stage(p.next, ab * kMergeThreads + threadIdx.x,
-                        ((int)gridDim.y - p.batch) * (int)gridDim.x * kMergeThreads);
+            apply_stage<kMergeThreads>(p.next, ab, ((int)gridDim.y - p.batch) * (int)gridDim.x);
             append_block<D, NEXT == 2>(p.next, ab);
             return;
         }
@@ -299,7 +298,11 @@ hipError_t launch_merge(const MergeParams &p, int head_dim, hipStream_t stream)
         const long long units = (long long)p.next.batch * p.next.num_kv_heads;
         next_blocks = p.next_kind == 2 ? append_blocks<true>(units) : append_blocks<false>(units);
     }
-    const unsigned x = (unsigned)((p.num_q_heads + per_block - 1) / per_block);
+    // A grid has at most 65535 rows; with few heads and thousands of sequences
+    // the append's workgroups take wider ones (the merge's beyond the heads exit).
+    unsigned x = (unsigned)((p.num_q_heads + per_block - 1) / per_block);
+    while (p.batch + (next_blocks + x - 1) / x > 65535)
+        x *= 2;
     const dim3 grid(x, (unsigned)(p.batch + (next_blocks + x - 1) / x));
     const dim3 block(kMergeThreads);
 #define SL_MERGE(DD, NN) hipLaunchKernelGGL((merge_kernel<DD, NN>), grid, block, 0, stream, p)

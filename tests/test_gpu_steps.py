@@ -130,3 +130,27 @@ def test_worker_counts_of_small_streams(D, kv, tiles):
                                         num_workers=workers)
         torch.cuda.synchronize()
         assert_parity(out, oracle_full(b), f"prefix {kv} tiles={tiles} workers={workers}")
+
+
+def test_e4m3_append_of_the_most_units():
+    """8192 sequences x 1024 heads: with two workgroups per unit more threads than a launch's first dimension holds."""
+    B, H, D = 8192, 1024, 64
+    _say("append units", B * H)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    rows = [torch.randn(B, H, D, generator=gen, device=DEV, dtype=torch.bfloat16) for _ in "kv"]
+    pages = [torch.full((B, H, 16, D), 0xAB, dtype=torch.uint8, device=DEV) for _ in "kv"]
+    scales = [torch.full((B, H), 7.0, device=DEV) for _ in "kv"]
+    table = torch.arange(B, dtype=torch.int32, device=DEV)[:, None].contiguous()
+    sl.kv_append(*rows, table, torch.ones(B, dtype=torch.int32, device=DEV), *pages, k_scales=scales[0],
+                 v_scales=scales[1])
+    torch.cuda.synchronize()
+    for x, p, s in zip(rows, pages, scales):
+        for i in range(0, B, 512):
+            f = x[i:i + 512].float()
+            a = f.abs().amax(dim=2)
+            want = a / torch.full_like(a, 448.0)   # (by a Python number torch multiplies by 1/448: another rounding)
+            codes = (f / want[:, :, None]).clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8)
+            assert torch.equal(s[i:i + 512], want)
+            assert torch.equal(p[i:i + 512, :, 0], codes)
+            assert bool((p[i:i + 512, :, 1:] == 0xAB).all())
