@@ -372,11 +372,16 @@ __device__ __forceinline__ void compute_step(Piece<D> &st, const Tile<D, FP8> (&
     }
     if (valid < kPageSize * NT) {
 #pragma unroll
-        for (int u = 0; u < NT; ++u)
+        for (int u = 0; u < NT; ++u) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (kPageSize * u + 4 * quad + r >= valid)
                     sc[u][r] = kNegInf;
+            // A missing tile carries the first one's scales: its zero weights must
+            // stay zero where that value scale is infinite.
+            if (FP8 && kPageSize * u >= valid)
+                vmul[u] = 1.0f;
+        }
     }
     // The head's maximum over the step (four lanes) is needed only when one of
     // them exceeds the running maximum by the slack: a wave-wide vote skips

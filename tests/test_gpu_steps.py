@@ -80,6 +80,29 @@ def test_scales_of_pages_not_read_do_not_leak(D, bad):
     assert_parity(out, want, f"D={D} bad={bad}")
 
 
+@pytest.mark.parametrize("pages", [1, 2, 3, 5, 6, 7, 9])
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_infinite_value_scale_beside_a_steps_missing_tiles(D, shared, pages):
+    """Full pages of positive values, the last one with an infinite value scale: every weighted sum is
+    +inf, as in the oracle, whether or not the unit's last step has tiles beyond its pages (a weight of
+    zero times the scale there would make it NaN)."""
+    _say("infinite scale", D, shared, pages)
+    b = inputs.make_paged_batch([16 * pages] * 2, 4, 2, D, seed=pages, device=DEV, kv_dtype="e4m3")
+    b.v_pages.bitwise_and_(0x3F).bitwise_or_(0x20)   # codes of 2^-3 up to 1.875
+    for i in range(2):
+        b.v_scales[b.block_table[i, pages - 1]] = float("inf")
+    if shared:   # both sequences read the first one's pages, through the shared stream
+        b.block_table[1] = b.block_table[0]
+        ints = dict(dtype=torch.int32, device=DEV)
+        out = sl.decode_attn_prefix_fp8(b.q, b.k_pages, b.v_pages, b.k_scales, b.v_scales, b.block_table, b.seq_lens,
+                                        b.scale, torch.tensor([0, 2], **ints), torch.tensor([pages], **ints))
+    else:
+        out = sl.run_batch(b)
+    torch.cuda.synchronize()
+    assert torch.isposinf(out.float()).all()
+
+
 @pytest.mark.parametrize("grow", ["none", "all", "some"])
 @pytest.mark.parametrize("D", [64, 128])
 def test_e4m3_append_at_every_slot(D, grow):
