@@ -260,12 +260,22 @@ __device__ __forceinline__ void issue_step(Step<D, FP8, NT> &st, const SplitPara
     }
 }
 
-// Regroup the K tile (loaded as whole 1 KB runs) into the score-MFMA layout
+// Regroup the K tiles (loaded as whole 1 KB runs) into the score-MFMA layout
 // through this wave's LDS buffer: lane (t, quad) needs row t, and for bf16
 // the 16-byte chunks 4 s + quad (s = 0 .. D/32 - 1), for FP8 the D/64 chunks
 // starting at quad D/64. A chunk c of row r is stored at position
 // c ^ ((r / P) % C) of its row (P rows per 256 bytes, C chunks per row), which
 // makes the 16-lane groups of both the writes and the reads hit distinct banks.
+//
+// A step's tiles pass through a buffer of one tile in turn: a wave's LDS
+// accesses take effect in the order it issues them, so a tile's writes need
+// not wait for the reads before them to return. (A buffer for all tiles of a
+// step is no faster where LDS is not short, and its 8 or 12 KB more per
+// workgroup cost the split and the prefix kernels their second workgroup per
+// CU: MI355X, E4M3, D = 128, prefix sharing of 1536 sequences in 768 groups
+// 186 us instead of 155; 256 sequences of 1..2048 tokens with 4096 workers 74
+// instead of 65. With 4096 sequences in more than 3862 groups the prefix kernel no
+// longer fitted a CU at all.)
 template <int D, bool FP8, int NT>
 __device__ __forceinline__ void regroup_k(const Tile<D, FP8> (&t)[NT], uint8_t *lds, int lane, int n, int quad,
                                           u32x4_t (&kc)[NT][FP8 ? D / 64 : D / 32])
@@ -273,23 +283,20 @@ __device__ __forceinline__ void regroup_k(const Tile<D, FP8> (&t)[NT], uint8_t *
     constexpr int R = D * (FP8 ? 1 : 2);   // bytes per row
     constexpr int C = R / 16;               // 16-byte chunks per row
     constexpr int P = 256 / R;              // rows per 256 bytes
+    const int key = (n / P) % C;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
 #pragma unroll
         for (int i = 0; i < Tile<D, FP8>::KW / 4; ++i) {
             const int off = 1024 * i + 16 * lane;
             const int r = off / R, c = (off % R) / 16;
-            *reinterpret_cast<u32x4_t *>(lds + u * kPageSize * R + r * R + 16 * (c ^ ((r / P) % C))) =
+            *reinterpret_cast<u32x4_t *>(lds + r * R + 16 * (c ^ ((r / P) % C))) =
                 u32x4_t{t[u].k[4 * i], t[u].k[4 * i + 1], t[u].k[4 * i + 2], t[u].k[4 * i + 3]};
         }
-    }
-    const int key = (n / P) % C;
-#pragma unroll
-    for (int u = 0; u < NT; ++u) {
 #pragma unroll
         for (int s = 0; s < (FP8 ? D / 64 : D / 32); ++s) {
             const int c = FP8 ? quad * (D / 64) + s : 4 * s + quad;
-            kc[u][s] = *reinterpret_cast<const u32x4_t *>(lds + u * kPageSize * R + n * R + 16 * (c ^ key));
+            kc[u][s] = *reinterpret_cast<const u32x4_t *>(lds + n * R + 16 * (c ^ key));
         }
     }
 }
@@ -814,7 +821,7 @@ template <int D, bool FP8>
 __device__ __forceinline__ uint8_t *k_regroup_stage()
 {
     __shared__ __attribute__((aligned(16)))
-    uint8_t k_stage[kWavesPerBlock][step_tiles<D, FP8>() * kPageSize * D * (FP8 ? 1 : 2)];
+    uint8_t k_stage[kWavesPerBlock][kPageSize * D * (FP8 ? 1 : 2)];
     return k_stage[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
 }
 

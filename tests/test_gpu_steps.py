@@ -177,3 +177,20 @@ def test_e4m3_append_of_the_most_units():
             assert torch.equal(s[i:i + 512], want)
             assert torch.equal(p[i:i + 512, :, 0], codes)
             assert bool((p[i:i + 512, :, 1:] == 0xAB).all())
+
+
+@pytest.mark.parametrize("D,kv", [k for k in KINDS if k != (128, "bf16")])
+def test_prefix_sharing_with_the_most_groups(D, kv):
+    """4096 sequences in 4096 groups, the most that are accepted: the kernel's arrays in LDS are at their largest."""
+    B = 4096
+    _say("most groups", D, kv)
+    b, starts, shared = inputs.make_grpo_batch(B, 1, 20, seed=4, device=DEV, num_q_heads=2, num_kv_heads=1, head_dim=D,
+                                               gen_median=10.0, gen_cap=40, kv_dtype=kv)
+    assert len(starts) == B + 1 and int(shared.min()) > 0
+    if kv == "e4m3":
+        out = sl.decode_attn_prefix_fp8(b.q, b.k_pages, b.v_pages, b.k_scales, b.v_scales, b.block_table, b.seq_lens,
+                                        b.scale, starts, shared)
+    else:
+        out = sl.decode_attn_prefix(b.q, b.k_pages, b.v_pages, b.block_table, b.seq_lens, b.scale, starts, shared)
+    torch.cuda.synchronize()
+    assert_parity(out, oracle_full(b), f"most groups D={D} {kv}")
