@@ -194,7 +194,7 @@ __device__ __forceinline__ void scan_prefix_groups(const SplitParams &p, const P
 
 // Both passes of prefix-shared attention in one launch (see the top of this
 // file). Every workgroup first derives both streams in its dynamic LDS
-// (prefix_dynamic_lds: 3 B + 2 S + 2 NG + 4 ints, S = pp.max_sub); the number of
+// (prefix_dynamic_lds: 3 B + 2 S + 3 ints, S = pp.max_sub); the number of
 // shared-page workers that take part is effective_shared_workers of the
 // own-page total, as in the merge.
 template <int D, bool FP8>
@@ -209,8 +209,13 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void prefix_split_kernel(Sp
     int32_t *const s_len = s_shared + B + 1;  // [B]
     int32_t *const s_sh = s_len + B;          // [S + 1]
     int32_t *const s_gl = s_sh + S + 1;       // [S]
-    int32_t *const s_gs = s_gl + S;           // [NG + 1]
-    int32_t *const s_sp = s_gs + pp.num_groups + 1;   // [NG]
+    // The groups' starts and pages, read by the scan alone: in the state queues,
+    // which are idle until then. (In dynamic LDS beside the rest, 4096 sequences
+    // in more than 3862 groups did not fit a CU with the 16 KB K stage of bf16,
+    // D = 128.)
+    static_assert(sizeof(int32_t) * (2 * kMaxPrefixBatch + 1) <= kWavesPerBlock * kOwnStageBytes, "the group arrays");
+    int32_t *const s_gs = reinterpret_cast<int32_t *>(own_state_stage());   // [NG + 1]
+    int32_t *const s_sp = s_gs + pp.num_groups + 1;                         // [NG]
     constexpr int NT = step_tiles<D, FP8>();
     scan_prefix_groups<NT>(own, pp, s_own, s_len, s_shared, s_sh, s_gl, s_gs, s_sp);
     if ((int)blockIdx.x < own_blocks)
@@ -235,7 +240,7 @@ hipError_t launch_prefix_split(const SplitParams &own, const SplitParams &shared
     const int own_blocks = (own.num_workers + kWavesPerBlock - 1) / kWavesPerBlock;
     const dim3 grid(own_blocks + max_shared);
     const dim3 block(kWave * kWavesPerBlock);
-    const size_t lds = prefix_dynamic_lds(own.batch, pp.max_sub, pp.num_groups);
+    const size_t lds = prefix_dynamic_lds(own.batch, pp.max_sub);
 #define SL_PREFIX(DD, FF) \
     hipLaunchKernelGGL((prefix_split_kernel<DD, FF>), grid, block, lds, stream, own, shared, pp, own_blocks, max_shared)
     if (head_dim == 128 && !fp8)

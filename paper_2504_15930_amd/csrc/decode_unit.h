@@ -674,6 +674,14 @@ __device__ __forceinline__ void flush_partial(const SplitParams &p, int head_dim
 constexpr int kOwnStageBytes = 8448;                        // per wave
 constexpr int kMaxOwnSlots = kOwnStageBytes / ((1 * (64 + 2) * 4 + 15) & ~15);
 
+// The workgroup's queues, one per wave. Idle until its workers start: the
+// prefix kernel keeps the groups' description here while it derives the streams.
+__device__ __forceinline__ uint8_t *own_state_stage()
+{
+    __shared__ __attribute__((aligned(16))) uint8_t own_stage[kWavesPerBlock * kOwnStageBytes];
+    return own_stage;
+}
+
 // Write `count` queued states: entry s holds G rows of D fp32 (acc) and G
 // pairs (m, l) as stage_partial lays them out; dest[s] = slot << 1 | (unit
 // area ? 1 : 0), the slot in (part_ml, part_acc) or (unit_ml, unit_acc).
@@ -888,9 +896,10 @@ __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, c
     bool part_staged = false;
     // Prefix own pages: the queue of finished own units' states (flush_states).
     constexpr bool kStageOwn = MODE == kOwnPages;
-    __shared__ uint8_t own_stage[kWavesPerBlock][kStageOwn ? kOwnStageBytes : 16];
     __shared__ uint32_t own_dest[kWavesPerBlock][kStageOwn ? kMaxOwnSlots : 1];
-    uint8_t *const qstage = own_stage[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
+    uint8_t *qstage = nullptr;
+    if constexpr (kStageOwn)
+        qstage = own_state_stage() + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * kOwnStageBytes;
     uint32_t *const qdest = own_dest[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
     const int own_slots = kStageOwn ? kOwnStageBytes / part_bytes : 0;   // 1 or more (G <= 16, D <= 128)
     int queued = 0;

@@ -179,7 +179,7 @@ def test_e4m3_append_of_the_most_units():
             assert bool((p[i:i + 512, :, 1:] == 0xAB).all())
 
 
-@pytest.mark.parametrize("D,kv", [k for k in KINDS if k != (128, "bf16")])
+@pytest.mark.parametrize("D,kv", KINDS)
 def test_prefix_sharing_with_the_most_groups(D, kv):
     """4096 sequences in 4096 groups, the most that are accepted: the kernel's arrays in LDS are at their largest."""
     B = 4096

@@ -67,7 +67,7 @@ def sizes(tmp_path_factory):
         '#include "sl_internal.h"\n'
         'extern "C" size_t split_bytes(int b) { return sl::split_dynamic_lds(b); }\n'
         'extern "C" size_t prefix_bytes(int b, int ng, int g)\n'
-        '{ return sl::prefix_dynamic_lds(b, sl::prefix_max_sub(b, ng, g), ng); }\n'
+        '{ return sl::prefix_dynamic_lds(b, sl::prefix_max_sub(b, ng, g)); }\n'
         'extern "C" int max_batch(int prefix) { return prefix ? sl::kMaxPrefixBatch : sl::kMaxBatch; }\n')
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     out = str(d / "sizes.so")
@@ -98,7 +98,7 @@ def test_two_split_workgroups_per_cu(static_lds, sizes, D, kv, batch):
     assert 2 * (_kernel(static_lds, "split_kv_kernel", D, kv) + sizes.split_bytes(batch)) <= LDS_PER_CU
 
 
-@pytest.mark.parametrize("D,kv", [k for k in KINDS if k != (128, "bf16")])
+@pytest.mark.parametrize("D,kv", KINDS)
 def test_prefix_kernel_fits_every_accepted_size(static_lds, sizes, D, kv):
     """Up to 4096 sequences in up to 4096 groups, 1 to 16 heads per KV head."""
     static, B = _kernel(static_lds, "prefix_split_kernel", D, kv), sizes.max_batch(1)
