@@ -9,10 +9,10 @@ namespace {
 template <int D, bool FP8>
 __global__ __launch_bounds__(kAppendThreads) void append_kernel(AppendParams p)
 {
-    const int blk = blockIdx.x * gridDim.y + blockIdx.y;
+    const int blk = blockIdx.x;
     // Nothing in this launch reads the lengths or the block table from memory in this mode.
     if (p.stage)
-        apply_stage<kAppendThreads>(p, blk, gridDim.x * gridDim.y);
+        apply_stage<kAppendThreads>(p, blk, gridDim.x);
     append_block<D, FP8>(p, blk);
 }
 
@@ -21,10 +21,8 @@ __global__ __launch_bounds__(kAppendThreads) void append_kernel(AppendParams p)
 hipError_t launch_append(const AppendParams &p, int head_dim, bool fp8, hipStream_t stream)
 {
     const long long units = (long long)p.batch * p.num_kv_heads;
-    // E4M3's two workgroups per unit lie along y: a dimension holds fewer than
-    // 2^32 threads, and there are fewer than 2^24 units.
-    const unsigned y = fp8 ? 2 : 1;
-    const dim3 grid((unsigned)((fp8 ? append_blocks<true>(units) : append_blocks<false>(units)) / y), y);
+    // Fewer than 2^24 units, so at most 2^22 workgroups: a dimension holds fewer than 2^32 threads.
+    const dim3 grid((unsigned)(fp8 ? append_blocks<true>(units) : append_blocks<false>(units)));
     const dim3 block(kAppendThreads);
     if (head_dim == 128 && !fp8)
         hipLaunchKernelGGL((append_kernel<128, false>), grid, block, 0, stream, p);

@@ -20,14 +20,17 @@
 // the codes are reproducible bit for bit.
 //
 // bf16: one wavefront per (sequence, KV head). E4M3: four wavefronts for its K
-// tile and four for its V tile, each re-encoding four of the tile's rows.
-// Lane l holds elements [l * D/64, (l + 1) * D/64) of the new row. The data
-// per call is a few KB per unit, so the kernel is bound by the latency of its
+// tile and four for its V tile, each re-encoding four of the tile's rows, or
+// with many units one wavefront for both tiles (kSpreadUnits). Lane l holds
+// elements [l * D/64, (l + 1) * D/64) of the new row. The data per call is a
+// few KB per unit, so with few units the kernel is bound by the latency of its
 // dependent loads (length -> block table -> scale and codes) and by the
 // arithmetic of a re-encoded tile (2048 true divisions and saturating
-// conversions). One wavefront that did K, then V, and fetched the old codes
-// only once it knew that the scale grows took 6.4 us for 96
-// sequences x 4 heads (MI355X); now 3.9.
+// conversions): for 96 sequences x 4 heads (MI355X) one wavefront per unit that
+// did K, then V took 6.4 us, eight wavefronts that fetch the old codes with the
+// scale 3.9.
+#include <type_traits>
+
 #include "sl_internal.h"
 #include "wave_ops.h"
 
@@ -76,29 +79,30 @@ __device__ __forceinline__ uint32_t f32x2_to_e4m3(float a, float b)
     return lo;
 }
 
-// Quantise-on-write of one row into one page-head tile (16 x D codes), by
-// four wavefronts (`part` 0..3; part k owns the tile's rows 4k .. 4k + 3) in
-// two phases. load() fetches the row, the scale and the part's old codes, all
-// in flight together; store() works out the new scale, the same in every
-// part, re-encodes the part's earlier rows if it grew, and writes the new row
-// in the part that owns its slot. Since store() overwrites the scale that
-// load() reads, every part's load must have returned (a barrier) before any
-// part's store.
-template <int D>
+// Quantise-on-write of one row into one page-head tile (16 x D codes), by P
+// wavefronts (`part` 0 .. P - 1; part k owns the tile's rows 16 k / P and on)
+// in two phases. load_row() and load_tile() fetch the row, the scale and, with
+// several parts, the part's old codes, all in flight together; store() works
+// out the new scale, the same in every part, re-encodes the part's earlier
+// rows if it grew, and writes the new row in the part that owns its slot.
+// Since store() overwrites the scale that load_tile() reads, every part's load
+// must have returned (a barrier) before any part's store. One wavefront alone
+// fetches the old codes only once it knows that the scale grows.
+template <int D, int P>
 struct AppendTile {
     static constexpr int E = D / kWave;             // row elements per lane (1 or 2)
-    static constexpr int W = D / 64;                // dwords of old codes per lane: 4 D codes over 64 lanes
-    static constexpr int kLaneRow = D / (4 * W);    // lanes per row of old codes
+    static constexpr int kRows = kPageSize / P;     // rows per part
+    // The part's old codes: a lane's own run of dwords with several parts (one
+    // load), a row after the other for one wavefront alone, which skips those
+    // past the slot.
+    using Word = std::conditional_t<(P > 1), uint32_t, std::conditional_t<D == 128, uint16_t, uint8_t>>;
+    static constexpr int kCodes = sizeof(Word);                 // codes per word
+    static constexpr int W = kRows * D / (kCodes * kWave);      // words per lane
+    __device__ static constexpr int word(int w, int lane) { return P > 1 ? W * lane + w : kWave * w + lane; }
     uint32_t x;
     float s_old;
-    uint32_t old[W];
+    Word old[P > 1 ? W : 1];
 
-    __device__ __forceinline__ void load(const uint16_t *row, const uint8_t *tile, const float *scale, int part,
-                                         int lane)
-    {
-        load_row(row, lane);
-        load_tile(tile, scale, part, lane);
-    }
     __device__ __forceinline__ void load_row(const uint16_t *row, int lane)
     {
         if constexpr (E == 2)
@@ -109,10 +113,12 @@ struct AppendTile {
     __device__ __forceinline__ void load_tile(const uint8_t *tile, const float *scale, int part, int lane)
     {
         s_old = *scale;
-        const uint32_t *codes = reinterpret_cast<const uint32_t *>(tile + 4 * part * D) + W * lane;
+        if constexpr (P > 1) {
+            const Word *codes = reinterpret_cast<const Word *>(tile + kRows * part * D);
 #pragma unroll
-        for (int w = 0; w < W; ++w)
-            old[w] = codes[w];
+            for (int w = 0; w < W; ++w)
+                old[w] = codes[word(w, lane)];
+        }
     }
     __device__ __forceinline__ void store(uint8_t *tile, float *scale, int slot, int part, int lane) const
     {
@@ -139,19 +145,31 @@ struct AppendTile {
         } else {
             s = a / 448.0f;
             // Re-encode the part's earlier rows with the grown scale.
-            if (4 * part + lane / kLaneRow < slot) {
-                uint32_t *codes = reinterpret_cast<uint32_t *>(tile + 4 * part * D) + W * lane;
+            Word *codes = reinterpret_cast<Word *>(tile + kRows * part * D);
+            auto earlier = [&](int w) { return kRows * part + kCodes * word(w, lane) / D < slot; };
+            uint32_t was[W];   // (set where it is read; zeros elsewhere would be waited for at the first load)
 #pragma unroll
-                for (int w = 0; w < W; ++w) {
-                    float r[4];
+            for (int w = 0; w < W; ++w) {
+                if constexpr (P > 1)
+                    was[w] = old[w];
+                else if (earlier(w))
+                    was[w] = codes[word(w, lane)];
+            }
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        r[c] = (e4m3_to_f32(old[w] >> (8 * c) & 0xffu) * s_old) / s;
-                    codes[w] = (f32x2_to_e4m3(r[0], r[1]) & 0xffffu) | f32x2_to_e4m3(r[2], r[3]) << 16;
+            for (int w = 0; w < W; ++w) {
+                if (!earlier(w))
+                    continue;
+                uint32_t now = 0;
+#pragma unroll
+                for (int c = 0; c < kCodes; c += 2) {
+                    const float r0 = (e4m3_to_f32(was[w] >> (8 * c) & 0xffu) * s_old) / s;
+                    const float r1 = kCodes > 1 ? (e4m3_to_f32(was[w] >> (8 * c + 8) & 0xffu) * s_old) / s : 0.0f;
+                    now |= (f32x2_to_e4m3(r0, r1) & 0xffffu) << (8 * c);
                 }
+                codes[word(w, lane)] = (Word)now;
             }
         }
-        if (part == slot / 4) {
+        if (part == slot / kRows) {
             if constexpr (E == 2)
                 *reinterpret_cast<uint16_t *>(tile + slot * D + 2 * lane) =
                     (uint16_t)f32x2_to_e4m3(v[0] / s, v[1] / s);
@@ -195,10 +213,10 @@ __device__ __forceinline__ bool append_valid(const AppendParams &p, int L, int p
 }
 
 // One of the K (`which` 0) and V (1) rows of unit `unit` = b * Hkv + g into
-// an E4M3 cache, by four wavefronts (part 0..3): AppendTile's two phases.
-template <int D>
+// an E4M3 cache, by P wavefronts (part 0 .. P - 1): AppendTile's two phases.
+template <int D, int P>
 struct AppendE4m3 {
-    AppendTile<D> t;
+    AppendTile<D, P> t;
     uint8_t *tile;
     float *scale;
 
@@ -235,13 +253,21 @@ __device__ __forceinline__ void append_place(const AppendParams &p, int b, int &
                : -1;
 }
 
-// Workgroups of kAppendThreads threads that append a step's rows: a wavefront
-// per unit for a bf16 cache, a workgroup per unit and K or V for E4M3.
+// Workgroups of kAppendThreads threads that append a step's rows. bf16 cache:
+// a wavefront per unit. E4M3: up to kSpreadUnits units, a workgroup per unit
+// and K or V; beyond them a wavefront per unit, which fills the chip just as
+// well and fetches the old codes (4 KB per unit of D = 128) only where the
+// scale grows. Spread -> one wavefront, calls of D = 128, MI355X:
+//   units                2048           3072           4096           16384         65536
+//   no scale grows        9.0 -> 9.1     9.5 -> 9.0    11.1 -> 9.1    36.6 -> 9.2   166 -> 25 us
+//   one scale in five     8.3 -> 9.6     9.6 -> 10.8   11.8 -> 12.0          22.0          60
+//   every scale          10.2 -> 10.4   13.5 -> 13.0   16.9 -> 15.2          36.9         116
 constexpr int kAppendThreads = 256;
+constexpr int kSpreadUnits = 2048;
 template <bool FP8>
 __host__ __device__ inline long long append_blocks(long long units)
 {
-    return FP8 ? 2 * units : (units + kAppendThreads / kWave - 1) / (kAppendThreads / kWave);
+    return FP8 && units <= kSpreadUnits ? 2 * units : (units + kAppendThreads / kWave - 1) / (kAppendThreads / kWave);
 }
 
 // Both rows of unit `unit` into a bf16 cache, by one wavefront.
@@ -265,18 +291,36 @@ __device__ __forceinline__ void append_unit_bf16(const AppendParams &p, int unit
     reinterpret_cast<uint32_t *>(static_cast<uint16_t *>(p.v_pages) + row)[lane] = vw;
 }
 
+// Both rows of unit `unit` into an E4M3 cache, by one wavefront.
+template <int D>
+__device__ __forceinline__ void append_unit_e4m3(const AppendParams &p, int unit, int lane)
+{
+    AppendE4m3<D, 1> k, v;
+    k.load_row(p, unit, 0, lane);   // beside the length and the page
+    v.load_row(p, unit, 1, lane);
+    const int b = unit / p.num_kv_heads;
+    int L, page;
+    append_place(p, b, L, page);
+    if (!append_valid(p, L, page))
+        return;
+    k.load_tile(p, unit - b * p.num_kv_heads, 0, page, 0, lane);
+    v.load_tile(p, unit - b * p.num_kv_heads, 1, page, 0, lane);
+    k.store(L, 0, lane);
+    v.store(L, 0, lane);
+}
+
 // Workgroup `blk` of append_blocks, run by its kAppendThreads threads.
 template <int D, bool FP8>
 __device__ __forceinline__ void append_block(const AppendParams &p, int blk)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     const int units = p.batch * p.num_kv_heads;
-    if constexpr (FP8) {
+    if (FP8 && units <= kSpreadUnits) {
         const int unit = blk >> 1, which = blk & 1;
         if (unit >= units)
             return;
         const int b = unit / p.num_kv_heads;
-        AppendE4m3<D> a;
+        AppendE4m3<D, 4> a;
         a.load_row(p, unit, which, lane);   // beside the length and the page
         int L, page;
         append_place(p, b, L, page);
@@ -288,11 +332,15 @@ __device__ __forceinline__ void append_block(const AppendParams &p, int blk)
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __syncthreads();
         a.store(L, wave, lane);
-    } else {
-        const int unit = blk * (kAppendThreads / kWave) + wave;
-        if (unit < units)
-            append_unit_bf16<D>(p, unit, lane);
+        return;
     }
+    const int unit = blk * (kAppendThreads / kWave) + wave;
+    if (unit >= units)
+        return;
+    if constexpr (FP8)
+        append_unit_e4m3<D>(p, unit, lane);
+    else
+        append_unit_bf16<D>(p, unit, lane);
 }
 
 }  // namespace

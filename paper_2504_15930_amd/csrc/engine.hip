@@ -173,7 +173,7 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
     // written once all of the unit's reads are done, these included.
     static_assert(kUnitWaves == 8, "four wavefronts each append K and V");
     const bool tail_append = FP8 && up.units_append && append_valid(up.next, L + 1, next_page);
-    AppendE4m3<D> app;
+    AppendE4m3<D, 4> app;
     if (tail_append) {
         app.load_row(up.next, b * Hkv + g, wave / 4, lane);
         app.load_tile(up.next, g, wave / 4, next_page, wave % 4, lane);

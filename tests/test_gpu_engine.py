@@ -351,3 +351,30 @@ def test_engine_units_in_one_some_and_many_workgroups(kv, Hq, Hkv, D, pages):
     a, b = got[False], got[True]
     ulp = torch.exp2(torch.floor(torch.log2(torch.maximum(a.abs(), b.abs()).clamp_min(2.0 ** -126))) - 7)
     assert torch.isfinite(a).all() and ((a - b).abs() <= 2 * ulp + 2.0 ** -7 * vmax).all()
+
+
+@pytest.mark.parametrize("kv,BS,Hkv", [("e4m3", 300, 8), ("e4m3", 256, 8), ("bf16", 300, 8)])
+def test_engine_append_beside_the_merge_of_many_slots(kv, BS, Hkv):
+    """Hundreds of slots (the E4M3 append spreads up to 2048 units over eight wavefronts each): steps run in one
+    call append the next step's rows in the merge's launch, steps run one call at a time in launches of
+    their own. Both leave the same cache, bit for bit."""
+    prompt = (np.arange(BS) % 50).astype(np.int32)
+    out = np.full(BS, 20, np.int32)
+    caches = []
+    for calls in (1, 20):
+        print("append beside the merge", kv, BS, calls, flush=True)
+        eng = E.Engine(prompt, out, out, batch_slots=BS, num_q_heads=Hkv, num_kv_heads=Hkv, head_dim=64,
+                       kv_fp8=kv == "e4m3", seed=7, row_sets=3)
+        scale = (4.0 ** torch.arange(3, device=DEV, dtype=torch.float32)).view(3, 1, 1, 1)
+        eng.k_new.copy_((eng.k_new.float() * scale).to(torch.bfloat16))
+        eng.v_new.copy_((eng.v_new.float() * scale).to(torch.bfloat16))
+        for t in (eng.k_pages, eng.v_pages):
+            t.zero_()
+        for _ in range(calls):
+            assert eng.run(20 // calls) == 20 // calls
+        torch.cuda.synchronize()
+        caches.append([t.cpu().clone() for t in (eng.k_pages, eng.v_pages, eng.seq_lens, eng.block_table)] +
+                      ([eng.k_scales.cpu().clone(), eng.v_scales.cpu().clone()] if kv == "e4m3" else []))
+        eng.close()
+    for x, y in zip(*caches):
+        assert torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8))

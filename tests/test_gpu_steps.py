@@ -103,16 +103,11 @@ def test_infinite_value_scale_beside_a_steps_missing_tiles(D, shared, pages):
     assert torch.isposinf(out.float()).all()
 
 
-@pytest.mark.parametrize("grow", ["none", "all", "some"])
-@pytest.mark.parametrize("D", [64, 128])
-def test_e4m3_append_at_every_slot(D, grow):
-    """A tile is re-encoded by four wavefronts of four rows each: every slot, with scales that stay,
-    grow, or grow in some heads, equals the oracle byte for byte; a fresh page ignores its old scale."""
+def _append_every_slot(D, grow, B, Hkv):
     rng = np.random.default_rng(D)
-    Hkv, lens = 3, np.arange(1, 34, dtype=np.int32)
-    B, N = len(lens), 3 * len(lens)
+    lens, N = np.arange(B, dtype=np.int32) % 33 + 1, 3 * B
     bt = rng.permutation(N).astype(np.int32).reshape(B, 3)
-    gain = {"none": 1e-3, "all": 50.0, "some": np.array([1e-3, 50.0, 1.0])[None, :, None]}[grow]
+    gain = {"none": 1e-3, "all": 50.0, "some": np.resize([1e-3, 50.0, 1.0], Hkv)[None, :, None]}[grow]
 
     def row():
         x = torch.from_numpy((rng.standard_normal((B, Hkv, D)) * gain).astype(np.float32)).to(torch.bfloat16)
@@ -129,6 +124,50 @@ def test_e4m3_append_at_every_slot(D, grow):
     torch.cuda.synchronize()
     for g, w in zip(got, want):
         assert np.array_equal(g.cpu().numpy().view(np.uint8), np.ascontiguousarray(w).view(np.uint8))
+
+
+@pytest.mark.parametrize("grow", ["none", "all", "some"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_e4m3_append_at_every_slot(D, grow):
+    """A tile is re-encoded by four wavefronts of four rows each: every slot, with scales that stay,
+    grow, or grow in some heads, equals the oracle byte for byte; a fresh page ignores its old scale."""
+    _append_every_slot(D, grow, 33, 3)
+
+
+@pytest.mark.parametrize("B,Hkv", [(512, 4), (683, 3), (825, 3)])
+@pytest.mark.parametrize("grow", ["none", "all", "some"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_e4m3_append_at_every_slot_of_many_units(D, grow, B, Hkv):
+    """The same around 2048 units, beyond which one wavefront re-encodes both of a unit's tiles."""
+    _append_every_slot(D, grow, B, Hkv)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_e4m3_append_of_many_units_is_not_bound_by_their_old_codes(D):
+    """65536 units whose scales stay: an E4M3 append stores half of a bf16 one's bytes and a scale per
+    row beside them, so it stays within a few times its duration (1.4 of it on MI355X; fetching every
+    unit's old codes took ten)."""
+    B, H = 8192, 8
+    _say("append duration", D)
+    rows = [torch.ones(B, H, D, dtype=torch.bfloat16, device=DEV) for _ in "kv"]
+    table = torch.arange(B, dtype=torch.int32, device=DEV)[:, None].contiguous()
+    lens = torch.full((B,), 9, dtype=torch.int32, device=DEV)
+    took = {}
+    for kv in ("bf16", "e4m3"):
+        dt = torch.bfloat16 if kv == "bf16" else torch.uint8
+        pages = [torch.zeros(B, H, 16, D, dtype=dt, device=DEV) for _ in "kv"]
+        kw = {} if kv == "bf16" else {n: torch.ones(B, H, device=DEV) for n in ("k_scales", "v_scales")}
+        times = []
+        for _ in range(12):
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                sl.kv_append(*rows, table, lens, *pages, **kw)
+            stop.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(stop))
+        took[kv] = sorted(times)[len(times) // 2]
+    assert took["e4m3"] < 4 * took["bf16"], took
 
 
 @pytest.mark.parametrize("tiles", [3, 4, 5, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 130])
