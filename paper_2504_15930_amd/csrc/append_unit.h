@@ -85,9 +85,10 @@ __device__ __forceinline__ uint32_t f32x2_to_e4m3(float a, float b)
 // several parts, the part's old codes, all in flight together; store() works
 // out the new scale, the same in every part, re-encodes the part's earlier
 // rows if it grew, and writes the new row in the part that owns its slot.
-// Since store() overwrites the scale that load_tile() reads, every part's load
-// must have returned (a barrier) before any part's store. One wavefront alone
-// fetches the old codes only once it knows that the scale grows.
+// Since store() overwrites the scale and the codes that load_tile() reads,
+// every part's load must have returned before any part's store: landed() and
+// a barrier. One wavefront alone fetches the old codes only once it knows that
+// the scale grows.
 template <int D, int P>
 struct AppendTile {
     static constexpr int E = D / kWave;             // row elements per lane (1 or 2)
@@ -119,6 +120,19 @@ struct AppendTile {
             for (int w = 0; w < W; ++w)
                 old[w] = codes[word(w, lane)];
         }
+    }
+    // Every load of load_tile() has returned, and its value is what store()
+    // uses: for the compiler the registers change here. (A barrier alone does
+    // not say so. The address of the scale is the same for the whole wavefront
+    // and this wavefront has stored nothing yet, so the compiler made it a
+    // scalar load and moved it to its first use, behind the barrier, where
+    // another part may have stored the grown scale already.)
+    __device__ __forceinline__ void landed()
+    {
+        asm volatile("" : "+v"(s_old));
+#pragma unroll
+        for (int w = 0; w < (P > 1 ? W : 0); ++w)
+            asm volatile("" : "+v"(old[w]));
     }
     __device__ __forceinline__ void store(uint8_t *tile, float *scale, int slot, int part, int lane) const
     {
@@ -231,6 +245,7 @@ struct AppendE4m3 {
         scale = (which ? p.v_scales : p.k_scales) + at;
         t.load_tile(tile, scale, part, lane);
     }
+    __device__ __forceinline__ void landed() { t.landed(); }
     __device__ __forceinline__ void store(int L, int part, int lane) const
     {
         t.store(tile, scale, (L - 1) % kPageSize, part, lane);
@@ -327,9 +342,7 @@ __device__ __forceinline__ void append_block(const AppendParams &p, int blk)
         if (!append_valid(p, L, page))      // the same for the whole workgroup
             return;
         a.load_tile(p, unit - b * p.num_kv_heads, which, page, wave, lane);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(0);      // this part's loads have returned
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        a.landed();
         __syncthreads();
         a.store(L, wave, lane);
         return;

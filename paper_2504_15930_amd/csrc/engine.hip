@@ -256,11 +256,8 @@ __device__ __forceinline__ void unit_attention(const UnitStepParams &up, const U
             state_ml[wave * kWave + lane] = f32x2_t{st.m, lsum};
         }
     }
-    if (tail_append) {   // (a wave without tiles has not waited for its loads yet)
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(0);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    }
+    if (tail_append)
+        app.landed();
     // (The library's barrier with a vote costs two barriers more and a load of
     // the launch's hidden arguments.)
     if (lane == 0)

@@ -1,0 +1,179 @@
+"""The engine's host plan of a one-launch step (CPU only), compiled for the host: the rule against a
+plain statement of it, its cost, and which of the kernel's merge branches the GPU tests' batches reach."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2504_15930_amd import build
+
+CUS = 256   # of an MI355X, and four (three for bf16 with head_dim 128) workers per CU
+SOURCE = r"""
+#include <chrono>
+#include <vector>
+#include "unit_plan.h"
+using namespace sl;
+// The rule, stated plainly: every share from the smallest one up.
+static int stepped(const int32_t *len, int n, int hkv, int cus, int workers, int32_t *first, uint32_t *split)
+{
+    if (n == 0 || (long long)n * hkv > cus)
+        return 0;
+    long long tiles = 0;
+    int longest = 0;
+    for (int e = 0; e < n; ++e) {
+        tiles += (len[e] + 15) / 16;
+        longest = std::max(longest, (len[e] + 15) / 16);
+    }
+    auto plan = [&](int share) {
+        const int per = kUnitWaves * share;
+        int blocks = 0;
+        for (int e = 0; e < n; ++e) {
+            const int nb = (len[e] + 15) / 16, k = (nb + per - 1) / per, waves = k * kUnitWaves;
+            if (k > kMaxUnitSplit)
+                return cus + 1;
+            first[e] = blocks;
+            split[e] = (uint32_t)(k - 1) | (uint32_t)(nb % waves) << 6 | (uint32_t)(nb / waves) << 16;
+            blocks += hkv * k;
+        }
+        first[n] = blocks;
+        return blocks;
+    };
+    const long long waves = (long long)cus * kUnitWaves, worker = (tiles * hkv + workers - 1) / workers;
+    int share = (int)std::max(1LL, (tiles * hkv + waves - 1) / waves), blocks;
+    while ((blocks = plan(share)) > cus)
+        share += std::max(1, share / 16);
+    auto cost = [&](int w) {
+        const int k = (longest + kUnitWaves * w - 1) / (kUnitWaves * w);
+        return w + (k > 1 ? kMergeTiles : 0) + (k - 1) / 8 * kMergeMoreTiles;
+    };
+    int best = share;
+    for (int k : {8, 1}) {
+        const int w = (longest + kUnitWaves * k - 1) / (kUnitWaves * k);
+        if (w > share && w <= worker + kUnitSlackTiles && cost(w) < cost(best))
+            best = w;
+    }
+    if (best != share)
+        blocks = plan(share = best);
+    const bool one_pass = share < 1 << 16 && share <= worker + kUnitSlackTiles;
+    // The whole part of every unit's share of the CUs instead: where one pass is refused, or
+    // leaves the longest wave more than twice the mean and more than this does.
+    if (one_pass && (double)share <= 2.0 * tiles * hkv / waves)
+        return blocks;
+    std::vector<int> ks(n);
+    int wave = 0, most_k = 1, total = 0;
+    for (int e = 0; e < n; ++e) {
+        const int nb = (len[e] + 15) / 16;
+        ks[e] = (int)std::max(1LL, std::min({(long long)cus * nb / (tiles * hkv), (nb + 7LL) / 8, 32LL}));
+        wave = std::max(wave, (nb + 8 * ks[e] - 1) / (8 * ks[e]));
+        most_k = std::max(most_k, ks[e]);
+        total += hkv * ks[e];
+    }
+    const int late = total > cus ? kSecondPassTiles : 0;
+    auto merging = [](int k) { return (k > 1 ? kMergeTiles : 0) + (k - 1) / 8 * kMergeMoreTiles; };
+    if (one_pass ? wave + merging(most_k) + late >= cost(share) : wave >= 1 << 16 || wave > worker + kUnitSlackTiles)
+        return one_pass ? blocks : 0;
+    total = 0;
+    for (int e = 0; e < n; ++e) {
+        const int nb = (len[e] + 15) / 16, k = ks[e];
+        first[e] = total;
+        split[e] = (uint32_t)(k - 1) | (uint32_t)(nb % (8 * k)) << 6 | (uint32_t)(nb / (8 * k)) << 16;
+        total += hkv * k;
+    }
+    return first[n] = total;
+}
+extern "C" int plan(int plain, const int32_t *len, int n, int hkv, int cus, int workers, int32_t *first, uint32_t *split)
+{
+    return (plain ? stepped : plan_units)(len, n, hkv, cus, workers, first, split);
+}
+extern "C" double microseconds(int plain, const int32_t *len, int n, int hkv, int cus, int workers)
+{
+    std::vector<int32_t> first(n + 1);
+    std::vector<uint32_t> split(n);
+    double best = 1e30;
+    for (int r = 0; r < 20; ++r) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (int i = 0; i < 100; ++i)
+            plan(plain, len, n, hkv, cus, workers, first.data(), split.data());
+        best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 100);
+    }
+    return best;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SOURCE)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    out = str(d / "plan.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I",
+                    os.path.join(rocm, "include"), "-I", build.CSRC, str(d / "plan.cpp"), "-o", out], check=True)
+    lib = ctypes.CDLL(out)
+    lib.microseconds.restype = ctypes.c_double
+    return lib
+
+
+def _plan(lib, lens, hkv, workers, cus=CUS, plain=False):
+    """(workgroups, first, split) of a step, or None for two launches."""
+    lens = np.ascontiguousarray(lens, np.int32)
+    first, split = np.full(len(lens) + 1, -1, np.int32), np.zeros(len(lens), np.uint32)
+    p = [a.ctypes.data_as(ctypes.c_void_p) for a in (lens, first, split)]
+    blocks = lib.plan(int(plain), p[0], len(lens), hkv, cus, workers, p[1], p[2])
+    return (blocks, first.tolist(), split.tolist()) if blocks else None
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_plan_is_the_rule(lib, seed):
+    rng = np.random.default_rng(seed)
+    one = 0
+    for _ in range(600):
+        hkv = int(rng.choice([1, 2, 3, 4, 8, 12]))
+        cus = int(rng.choice([256, 256, 64, 304]))
+        n = int(rng.integers(1, max(2, min(128, cus // hkv + 2))))
+        lens = rng.integers(1, int(rng.choice([17, 300, 5000, 60000])), n)
+        if rng.random() < .5:
+            lens[rng.integers(0, n)] = int(rng.integers(1, 500000))
+        workers = int(rng.choice([768, 1024, 1, 100, 4096]))
+        got, want = (_plan(lib, lens, hkv, workers, cus, plain) for plain in (False, True))
+        assert got == want, (hkv, cus, workers, lens.tolist())
+        one += got is not None
+    assert one > 100
+
+
+def test_plan_covers_every_unit(lib):
+    """The workgroups of a plan: in order, at most two for each CU, and their waves' shares add up to
+    the unit's pages."""
+    rng = np.random.default_rng(9)
+    for _ in range(600):
+        lens = rng.integers(1, 9000, rng.integers(1, 60))
+        if rng.random() < .5:
+            lens = lens // 50 + 1
+            lens[0] = rng.integers(1, 100000)
+        got = _plan(lib, lens, 4, 768)
+        if got is None:
+            continue
+        blocks, first, split = got
+        assert first[0] == 0 and first[-1] == blocks <= 2 * CUS
+        for e, L in enumerate(lens):
+            k, rem, per = (split[e] & 63) + 1, split[e] >> 6 & 1023, split[e] >> 16
+            assert first[e + 1] - first[e] == 4 * k and k <= 32 and rem < 8 * k
+            assert per * 8 * k + rem == -(-int(L) // 16)
+
+
+def test_one_long_sequence_among_many_short_ones_takes_one_launch(lib):
+    """Also where the units, a workgroup each, fill the chip: two launches were slower."""
+    for lens, hkv in (([32000] + [200] * 127, 2), ([16000] + [100] * 63, 4)):
+        for workers in (768, 1024):
+            blocks, first, split = _plan(lib, lens, hkv, workers)
+            assert blocks > CUS and (split[0] & 63) == 31
+
+
+def test_plan_of_one_long_sequence_among_many_costs_little(lib):
+    """Trying share after share costs many times the plan's passes."""
+    lens = np.array([32000] + [200] * 127, np.int32)
+    p = lens.ctypes.data_as(ctypes.c_void_p)
+    ours, plain = (lib.microseconds(v, p, len(lens), 2, CUS, 768) for v in (0, 1))
+    assert ours < plain / 5, (ours, plain)

@@ -1,8 +1,9 @@
-"""LDS of the split kernels against what a gfx950 CU holds (CPU only): the static part from the
-metadata of the built library's code objects, the dynamic part from the functions that the launches
-use. Nothing is launched."""
+"""The built library's GPU code, read on the CPU (nothing is launched): LDS of the split kernels against
+what a gfx950 CU holds, the static part from the metadata of the code objects, the dynamic part from
+the functions that the launches use; and what the append's barrier stands between."""
 import ctypes
 import os
+import re
 import struct
 import subprocess
 
@@ -112,3 +113,28 @@ def test_two_prefix_workgroups_per_cu(static_lds, sizes, D, kv, batch, groups, g
     """The shared pages stream beside the own ones: two workgroups on a CU."""
     one = _kernel(static_lds, "prefix_split_kernel", D, kv) + sizes.prefix_bytes(batch, groups, group)
     assert 2 * one <= LDS_PER_CU
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_e4m3_append_loads_the_old_scale_before_its_barrier(tmp_path, D):
+    """Four wavefronts re-encode a tile whose scale one of them overwrites after the barrier: no load that
+    the compiler holds to be unaffected by stores (a scalar one) may come after it."""
+    objdump = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump under ROCm here")
+    if not os.path.exists(sl.LIBRARY):
+        build.build()
+    found = 0
+    for i, elf in enumerate(_code_objects(open(sl.LIBRARY, "rb").read())):
+        path = tmp_path / f"{i}.elf"
+        path.write_bytes(elf)
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True,
+                              check=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\S+)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", text, re.S | re.M):
+            if f"append_kernelILi{D}ELb1E" not in name:
+                continue
+            found += 1
+            before, _, after = body.partition("s_barrier")
+            assert after, "the barrier"
+            assert not re.findall(r"\bs_(?:buffer_)?load\S*.*", after)
+    assert found == 1
