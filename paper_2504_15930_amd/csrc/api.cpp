@@ -237,11 +237,9 @@ sl_status run(const sl_attn_desc *d, const uint16_t *q, const void *k_pages, con
     mp.step_tiles = split_step_tiles(d->head_dim, fp8);
     mp.group_inverse = inverse_of(G);
     mp.fp8 = fp8;
-    mp.next_kind = 0;
-    if (next) {
+    mp.has_next = next != nullptr;
+    if (next)
         mp.next = *next;
-        mp.next_kind = fp8 ? 2 : 1;
-    }
     if (launch_merge(mp, d->head_dim, d->stream) != hipSuccess)
         return SL_ERR_HIP;
     return SL_OK;

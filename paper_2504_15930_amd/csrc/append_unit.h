@@ -277,12 +277,19 @@ __device__ __forceinline__ void append_place(const AppendParams &p, int b, int &
 //   no scale grows        9.0 -> 9.1     9.5 -> 9.0    11.1 -> 9.1    36.6 -> 9.2   166 -> 25 us
 //   one scale in five     8.3 -> 9.6     9.6 -> 10.8   11.8 -> 12.0          22.0          60
 //   every scale          10.2 -> 10.4   13.5 -> 13.0   16.9 -> 15.2          36.9         116
+// Each is a kernel of its own: together their code reached the merge's launch,
+// whose append has 1024 units for 256 sequences x 4 heads, 1.3 us later.
 constexpr int kAppendThreads = 256;
 constexpr int kSpreadUnits = 2048;
-template <bool FP8>
-__host__ __device__ inline long long append_blocks(long long units)
+enum AppendKind { kNoAppend, kAppendBf16, kAppendSpread, kAppendWave };
+inline AppendKind append_kind(const AppendParams &p, bool fp8)
 {
-    return FP8 && units <= kSpreadUnits ? 2 * units : (units + kAppendThreads / kWave - 1) / (kAppendThreads / kWave);
+    return !fp8 ? kAppendBf16 : (long long)p.batch * p.num_kv_heads <= kSpreadUnits ? kAppendSpread : kAppendWave;
+}
+inline long long append_blocks(const AppendParams &p, AppendKind kind)
+{
+    const long long units = (long long)p.batch * p.num_kv_heads;
+    return kind == kAppendSpread ? 2 * units : (units + kAppendThreads / kWave - 1) / (kAppendThreads / kWave);
 }
 
 // Both rows of unit `unit` into a bf16 cache, by one wavefront.
@@ -325,12 +332,12 @@ __device__ __forceinline__ void append_unit_e4m3(const AppendParams &p, int unit
 }
 
 // Workgroup `blk` of append_blocks, run by its kAppendThreads threads.
-template <int D, bool FP8>
+template <int D, int KIND>
 __device__ __forceinline__ void append_block(const AppendParams &p, int blk)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     const int units = p.batch * p.num_kv_heads;
-    if (FP8 && units <= kSpreadUnits) {
+    if constexpr (KIND == kAppendSpread) {
         const int unit = blk >> 1, which = blk & 1;
         if (unit >= units)
             return;
@@ -345,15 +352,15 @@ __device__ __forceinline__ void append_block(const AppendParams &p, int blk)
         a.landed();
         __syncthreads();
         a.store(L, wave, lane);
-        return;
+    } else {
+        const int unit = blk * (kAppendThreads / kWave) + wave;
+        if (unit >= units)
+            return;
+        if constexpr (KIND == kAppendWave)
+            append_unit_e4m3<D>(p, unit, lane);
+        else
+            append_unit_bf16<D>(p, unit, lane);
     }
-    const int unit = blk * (kAppendThreads / kWave) + wave;
-    if (unit >= units)
-        return;
-    if constexpr (FP8)
-        append_unit_e4m3<D>(p, unit, lane);
-    else
-        append_unit_bf16<D>(p, unit, lane);
 }
 
 }  // namespace

@@ -153,17 +153,17 @@ __device__ __forceinline__ int kv_head(int h, int group, uint32_t group_inverse)
     return group == 1 ? h : (int)(((uint64_t)(uint32_t)h * group_inverse) >> 32);
 }
 
-// NEXT: the decode engine's next-step append in the same launch (0 none,
-// 1 bf16 cache, 2 E4M3 cache), in the workgroups after the merge's.
+// NEXT: the decode engine's next-step append in the same launch (an
+// AppendKind), in the workgroups after the merge's.
 template <int D, int NEXT>
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p)
 {
     const int b = blockIdx.y;   // rows of workgroups: one per sequence, then the append's
-    if constexpr (NEXT != 0) {
+    if constexpr (NEXT != kNoAppend) {
         if (b >= p.batch) {
             const int ab = (b - p.batch) * (int)gridDim.x + (int)blockIdx.x;
             apply_stage<kMergeThreads>(p.next, ab, ((int)gridDim.y - p.batch) * (int)gridDim.x);
-            append_block<D, NEXT == 2>(p.next, ab);
+            append_block<D, NEXT>(p.next, ab);
             return;
         }
     }
@@ -293,11 +293,8 @@ hipError_t launch_merge(const MergeParams &p, int head_dim, hipStream_t stream)
 {
     const int per_block = kMergeThreads / kWave;
     static_assert(kMergeThreads == kAppendThreads, "the append's workgroups ride in the merge's launch");
-    long long next_blocks = 0;
-    if (p.next_kind != 0) {
-        const long long units = (long long)p.next.batch * p.next.num_kv_heads;
-        next_blocks = p.next_kind == 2 ? append_blocks<true>(units) : append_blocks<false>(units);
-    }
+    const AppendKind kind = p.has_next ? append_kind(p.next, p.fp8 != 0) : kNoAppend;
+    const long long next_blocks = p.has_next ? append_blocks(p.next, kind) : 0;
     // A grid has at most 65535 rows; with few heads and thousands of sequences
     // the append's workgroups take wider ones (the merge's beyond the heads exit).
     unsigned x = (unsigned)((p.num_q_heads + per_block - 1) / per_block);
@@ -305,20 +302,18 @@ hipError_t launch_merge(const MergeParams &p, int head_dim, hipStream_t stream)
         x *= 2;
     const dim3 grid(x, (unsigned)(p.batch + (next_blocks + x - 1) / x));
     const dim3 block(kMergeThreads);
-#define SL_MERGE(DD, NN) hipLaunchKernelGGL((merge_kernel<DD, NN>), grid, block, 0, stream, p)
-    if (head_dim == 128 && p.next_kind == 0)
-        SL_MERGE(128, 0);
-    else if (head_dim == 128 && p.next_kind == 1)
-        SL_MERGE(128, 1);
-    else if (head_dim == 128 && p.next_kind == 2)
-        SL_MERGE(128, 2);
-    else if (head_dim == 64 && p.next_kind == 0)
-        SL_MERGE(64, 0);
-    else if (head_dim == 64 && p.next_kind == 1)
-        SL_MERGE(64, 1);
-    else if (head_dim == 64 && p.next_kind == 2)
-        SL_MERGE(64, 2);
+#define SL_MERGE(DD, NN) \
+    if (head_dim == DD && kind == NN) \
+        hipLaunchKernelGGL((merge_kernel<DD, NN>), grid, block, 0, stream, p); \
     else
+    SL_MERGE(128, kNoAppend)
+    SL_MERGE(128, kAppendBf16)
+    SL_MERGE(128, kAppendSpread)
+    SL_MERGE(128, kAppendWave)
+    SL_MERGE(64, kNoAppend)
+    SL_MERGE(64, kAppendBf16)
+    SL_MERGE(64, kAppendSpread)
+    SL_MERGE(64, kAppendWave)
         return hipErrorInvalidValue;
 #undef SL_MERGE
     return hipGetLastError();

@@ -240,12 +240,12 @@ struct MergeParams {
     int32_t fp8;
     uint32_t group_inverse;   // as PrefixMergeParams'
     // Decode engine: the next step's staged append (and its bookkeeping) runs
-    // in the same launch, in workgroups after the merge's; 0 none, 1 bf16
-    // cache, 2 E4M3 cache. The merge never reads what it writes: it reads the
+    // in the same launch, in workgroups after the merge's, if has_next is set.
+    // The merge never reads what it writes: it reads the
     // lengths only for sequences without pages, whose rows are zero whatever
     // the step (the engine's lengths are never negative).
     AppendParams next;
-    int32_t next_kind;
+    int32_t has_next;
 };
 
 
