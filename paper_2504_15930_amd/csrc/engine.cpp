@@ -34,6 +34,7 @@
 #include "sl_engine.h"
 #include "api_internal.h"
 #include "engine_internal.h"
+#include "unit_plan.h"
 
 namespace {
 
@@ -48,21 +49,7 @@ using sl::kPageSize;
 constexpr int kRing = 8;
 constexpr int kRingGroup = 4;
 constexpr int kRingEvents = kRing / kRingGroup;
-// One-launch step: taken only while its longest wave range is within
-// kUnitSlackTiles tiles of a split-kernel worker's share (the two-launch
-// step spreads tiles over all workers but pays a second launch).
 constexpr int kUnitThreads = sl::kUnitWaves * sl::kWave;
-constexpr int kUnitSlackTiles = 8;
-// What merging a unit's pieces costs, in tiles of a wave's stream: once the
-// unit has more than one workgroup, and again per eight workgroups more.
-// Generations with kMergeTiles / kMergeMoreTiles of 2 / 1, 4 / 1, 2 / 2, 4 / 2
-// and 5 / 2 (MI355X, ms; without the rule 30.2, 27.1, 4.6 and 36.4):
-//   96 samples on 32 slots, bf16        30.1   30.0   29.3   29.1   29.4
-//   the same, E4M3                      26.7   26.7   25.5   25.2   25.3
-//   2 short samples on one slot, bf16    4.5    4.3    4.6    4.2    4.2
-//   32 samples on 24 slots, 64/8 heads  36.2   36.2   33.7   33.7   33.7
-constexpr int kMergeTiles = 4;
-constexpr int kMergeMoreTiles = 2;
 
 bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
@@ -252,8 +239,7 @@ bool sl_engine::plan_unit_step(const Staged &sg)
     if (!unit_mem)
         return false;
     const int32_t *h = h_stage[sg.ring];
-    int n = 0, z = 0, longest = 0;
-    long long tiles = 0;   // per KV head
+    int n = 0, z = 0;
     for (int b = 0; b < BS; ++b) {
         if (h[b] > 0) {
             if (n == sl::kMaxUnitEntries)
@@ -261,62 +247,15 @@ bool sl_engine::plan_unit_step(const Staged &sg)
             up.seq[n] = b;
             up.len[n] = h[b];
             ++n;
-            const int nb = (h[b] + kPageSize - 1) / kPageSize;
-            tiles += nb;
-            longest = std::max(longest, nb);
         } else if (!zeroed[b]) {
             if (z == sl::kMaxUnitEntries)
                 return false;
             up.zero[z++] = b;
         }
     }
-    if (n == 0 || (long long)n * Hkv > cus)
-        return false;
-    // Workgroups per unit: the fewest that leave every wave at most wave_tiles
-    // tiles, and with wave_tiles the smallest (to a sixteenth) whose workgroups
-    // fit the chip in one pass: the longest wave sets the stream's time.
-    // (Giving every unit the whole part of its share of the CUs left some waves
-    // with nearly twice the tiles of others: a 96-sample generation took 33.2
-    // instead of 32.5 ms.)
-    auto plan = [&](int wave_tiles) {   // the workgroups, or more than the chip holds
-        const int per = sl::kUnitWaves * wave_tiles;
-        int blocks = 0;
-        for (int e = 0; e < n; ++e) {
-            const int nb = (up.len[e] + kPageSize - 1) / kPageSize;
-            const int k = (nb + per - 1) / per, waves = k * sl::kUnitWaves;
-            if (k > sl::kMaxUnitSplit)
-                return cus + 1;
-            up.first[e] = blocks;
-            up.split[e] = (uint32_t)(k - 1) | (uint32_t)(nb % waves) << 6 | (uint32_t)(nb / waves) << 16;
-            blocks += Hkv * k;
-        }
-        up.first[n] = blocks;
-        return blocks;
-    };
-    const long long all_waves = (long long)cus * sl::kUnitWaves;
-    int wave_tiles = (int)std::max(1LL, (tiles * Hkv + all_waves - 1) / all_waves);
-    int blocks = 0;
-    while ((blocks = plan(wave_tiles)) > cus)
-        wave_tiles += std::max(1, wave_tiles / 16);
-    const long long worker_tiles = (tiles * Hkv + nw - 1) / nw;
-    // Fewer and longer shares can still be faster, as the pieces of a unit cost
-    // a merge: the units in at most eight workgroups each (one batch of loads
-    // for whoever merges them), or in one (no merge).
-    auto cost = [longest](int w) {
-        const int k = (longest + sl::kUnitWaves * w - 1) / (sl::kUnitWaves * w);
-        return w + (k > 1 ? kMergeTiles : 0) + (k - 1) / 8 * kMergeMoreTiles;
-    };
-    int best = wave_tiles;
-    for (const int k : {8, 1}) {
-        const int w = (longest + sl::kUnitWaves * k - 1) / (sl::kUnitWaves * k);
-        if (w > wave_tiles && w <= worker_tiles + kUnitSlackTiles && cost(w) < cost(best))
-            best = w;
-    }
-    if (best != wave_tiles)
-        blocks = plan(wave_tiles = best);
-    if (wave_tiles >= 1 << 16)   // the quotients' field
-        return false;
-    if (blocks > sl::kMaxUnitBlocks || wave_tiles > worker_tiles + kUnitSlackTiles)
+    const int tile_bytes = 2 * kPageSize * D * (fp8 ? 1 : 2);
+    const int blocks = sl::plan_units(up.len, n, Hkv, cus, nw, tile_bytes, up.first, up.split);
+    if (blocks == 0 || blocks > sl::kMaxUnitBlocks)
         return false;
     up.n_entries = n;
     up.unit_blocks = blocks;

@@ -23,9 +23,16 @@ constexpr int kUnitSlackTiles = 8;
 constexpr int kMergeTiles = 4;
 constexpr int kMergeMoreTiles = 2;
 // What workgroups beyond the chip's first pass cost, in the same tiles: they
-// start late (53 short and long sequences, 320 workgroups with waves of 3
-// tiles instead of 248 with 7: 11.6 us a step instead of 11.1).
-constexpr int kSecondPassTiles = 4;
+// start late (46 sequences x 4 KV heads, a fifth of them long, E4M3: 304
+// workgroups with waves of 5 tiles 13.2 us a step, 224 with 9 12.7).
+constexpr int kSecondPassTiles = 6;
+
+// The most a wave streams in a plan that does not fit the chip in one pass:
+// with more, waves that end unevenly cost more than a second launch (122
+// sequences x 2 KV heads, a fifth of them long, bf16 with head_dim 128, waves of
+// 11 tiles = 88 KB: 40.7 us a step, 36.7 in two launches; 25 x 8, head_dim 64,
+// 51 tiles = 204 KB: 87 and 70; 49 x 4, head_dim 64, 15 tiles = 60 KB: 24.6 and 28.8).
+constexpr int kSecondPassBytes = 64 << 10;
 
 inline int merge_cost(int k) { return (k > 1 ? kMergeTiles : 0) + (k - 1) / 8 * kMergeMoreTiles; }
 
@@ -66,10 +73,16 @@ inline int one_pass_share(const int32_t *len, int n, int num_kv_heads, int cus, 
     // of host time per step for 128 sequences, one of them long; now 0.2.)
     const long long all_waves = (long long)cus * kUnitWaves;
     int wave_tiles = (int)std::max(1LL, (tiles * num_kv_heads + all_waves - 1) / all_waves);
-    if (wave_tiles > most || !fits(most))
+    if (wave_tiles > most)
         return 0;
-    int lo = wave_tiles, hi = most;   // hi fits
-    while (lo < hi) {
+    int lo = wave_tiles, hi = wave_tiles;
+    if (!fits(lo)) {   // (most small steps fit at once)
+        if (!fits(most))
+            return 0;
+        ++lo;
+        hi = most;
+    }
+    while (lo < hi) {   // hi fits
         const int mid = lo + (hi - lo) / 2;
         if (fits(mid))
             hi = mid;
@@ -94,21 +107,25 @@ inline int one_pass_share(const int32_t *len, int n, int num_kv_heads, int cus, 
 }
 
 // Plan n sequences (len[e] >= 1) with num_kv_heads units each on `cus` CUs;
-// `workers` is the two-launch step's worker count. Fills first[0 .. n] and
+// `workers` is the two-launch step's worker count, tile_bytes what a wave reads
+// per tile (K and V). Fills first[0 .. n] and
 // split[0 .. n) (UnitStepParams) and returns the workgroups, or 0 for two
 // launches.
 //
 // The units get the fewest workgroups that leave every wave at most
-// one_pass_share tiles. With one long sequence among so many short ones that
+// one_pass_share tiles. With a few long sequences among so many short ones that
 // their units, a workgroup each, fill most of the chip, there is no such plan,
 // or its longest wave has far more than the mean. Every unit then gets the
-// whole part of its share of the CUs, if that leaves less to the longest wave:
-// the few workgroups too many start as the short ones end. Per step, MI355X:
-//   128 sequences x 2 KV heads, 32000 and 200.. tokens    20.9 us; in two launches 28.7
-//   the same, E4M3                                        16.2; in two launches 26.7
-//   53 x 4, lognormal up to 40000, longest wave 77 tiles  132 us; in one pass (106 tiles) 148
-inline int plan_units(const int32_t *len, int n, int num_kv_heads, int cus, int workers, int32_t *first,
-                      uint32_t *split)
+// whole part of its share of the CUs, as long as the workgroups too many start
+// when the short ones end, within kSecondPassBytes and with the longest wave
+// near the mean (a second launch counted as kUnitSlackTiles, and the rounds a
+// quarter longer than their waves say). Per step, MI355X, in one pass or two
+// launches -> with such a plan:
+//   128 sequences x 2 KV heads, 32000 and 200.. tokens     28.7 -> 20.9 us; E4M3 26.7 -> 16.2
+//   54 x 4, one to three of 32000, the others short, E4M3  31.8 -> 26.4
+//   53 x 4, lognormal up to 40000                           148 -> 129
+inline int plan_units(const int32_t *len, int n, int num_kv_heads, int cus, int workers, int tile_bytes,
+                      int32_t *first, uint32_t *split)
 {
     if (n == 0 || (long long)n * num_kv_heads > cus)
         return 0;
@@ -132,8 +149,9 @@ inline int plan_units(const int32_t *len, int n, int num_kv_heads, int cus, int 
         }
         return first[n] = blocks;
     };
-    if (share == 0 || (long long)share * cus * kUnitWaves > 2 * tiles * num_kv_heads) {
-        int wave = 0, most_groups = 1;
+    const long long all_waves = (long long)cus * kUnitWaves;
+    if (share == 0 || (share > kSecondPassTiles + 1 && share * all_waves > 2 * tiles * num_kv_heads)) {
+        int wave = 0, most_groups = 1, long_blocks = 0;
         const int blocks = place([&](int nb) {
             const int whole = (int)std::min((long long)cus * nb / (tiles * num_kv_heads), (long long)kMaxUnitSplit);
             const int k = std::max(1, std::min(whole, (nb + kUnitWaves - 1) / kUnitWaves));
@@ -141,9 +159,18 @@ inline int plan_units(const int32_t *len, int n, int num_kv_heads, int cus, int 
             most_groups = std::max(most_groups, k);
             return k;
         });
+        if (wave >= 1 << 16)
+            return 0;
+        for (int e = 0; e < n; ++e)   // those with more than half of the longest wave
+            if (2 * (int)(split[e] >> 16) >= wave)
+                long_blocks += first[e + 1] - first[e];
+        const long long rounds = (long long)wave * std::max(1, (long_blocks + cus - 1) / cus);
         if (share == 0)
-            return wave <= most ? blocks : 0;
-        if (wave + merge_cost(most_groups) + (blocks > cus ? kSecondPassTiles : 0) <
+            return rounds * tile_bytes <= kSecondPassBytes &&
+                           5 * rounds * all_waves <= 4 * (tiles * num_kv_heads + kUnitSlackTiles * all_waves)
+                       ? blocks
+                       : 0;
+        if (rounds + merge_cost(most_groups) + (blocks > cus ? kSecondPassTiles : 0) <
             share + merge_cost(groups_of(longest, share)))
             return blocks;
     }

@@ -16,7 +16,7 @@ SOURCE = r"""
 #include "unit_plan.h"
 using namespace sl;
 // The rule, stated plainly: every share from the smallest one up.
-static int stepped(const int32_t *len, int n, int hkv, int cus, int workers, int32_t *first, uint32_t *split)
+static int stepped(const int32_t *len, int n, int hkv, int cus, int workers, int bytes, int32_t *first, uint32_t *split)
 {
     if (n == 0 || (long long)n * hkv > cus)
         return 0;
@@ -57,22 +57,30 @@ static int stepped(const int32_t *len, int n, int hkv, int cus, int workers, int
     if (best != share)
         blocks = plan(share = best);
     const bool one_pass = share < 1 << 16 && share <= worker + kUnitSlackTiles;
-    // The whole part of every unit's share of the CUs instead: where one pass is refused, or
-    // leaves the longest wave more than twice the mean and more than this does.
-    if (one_pass && (double)share <= 2.0 * tiles * hkv / waves)
+    // The whole part of every unit's share of the CUs instead: where one pass is refused and this
+    // takes little more than the mean, or where one pass leaves the longest wave more than twice
+    // the mean and more than this does.
+    if (one_pass && (share <= kSecondPassTiles + 1 || (double)share <= 2.0 * tiles * hkv / waves))
         return blocks;
-    std::vector<int> ks(n);
-    int wave = 0, most_k = 1, total = 0;
+    std::vector<int> ks(n), least(n);
+    int wave = 0, most_k = 1, total = 0, longer = 0;
     for (int e = 0; e < n; ++e) {
         const int nb = (len[e] + 15) / 16;
         ks[e] = (int)std::max(1LL, std::min({(long long)cus * nb / (tiles * hkv), (nb + 7LL) / 8, 32LL}));
+        least[e] = nb / (8 * ks[e]);
         wave = std::max(wave, (nb + 8 * ks[e] - 1) / (8 * ks[e]));
         most_k = std::max(most_k, ks[e]);
         total += hkv * ks[e];
     }
-    const int late = total > cus ? kSecondPassTiles : 0;
+    if (wave >= 1 << 16)
+        return 0;
+    for (int e = 0; e < n; ++e)
+        longer += 2 * least[e] >= wave ? hkv * ks[e] : 0;
+    const double rounds = (double)wave * std::max(1, (longer + cus - 1) / cus);
     auto merging = [](int k) { return (k > 1 ? kMergeTiles : 0) + (k - 1) / 8 * kMergeMoreTiles; };
-    if (one_pass ? wave + merging(most_k) + late >= cost(share) : wave >= 1 << 16 || wave > worker + kUnitSlackTiles)
+    const int late = total > cus ? kSecondPassTiles : 0;
+    if (one_pass ? rounds + merging(most_k) + late >= cost(share)
+                 : rounds * bytes > kSecondPassBytes || 1.25 * rounds > (double)tiles * hkv / waves + kUnitSlackTiles)
         return one_pass ? blocks : 0;
     total = 0;
     for (int e = 0; e < n; ++e) {
@@ -83,11 +91,12 @@ static int stepped(const int32_t *len, int n, int hkv, int cus, int workers, int
     }
     return first[n] = total;
 }
-extern "C" int plan(int plain, const int32_t *len, int n, int hkv, int cus, int workers, int32_t *first, uint32_t *split)
+extern "C" int plan(int plain, const int32_t *len, int n, int hkv, int cus, int workers, int bytes, int32_t *first,
+                    uint32_t *split)
 {
-    return (plain ? stepped : plan_units)(len, n, hkv, cus, workers, first, split);
+    return (plain ? stepped : plan_units)(len, n, hkv, cus, workers, bytes, first, split);
 }
-extern "C" double microseconds(int plain, const int32_t *len, int n, int hkv, int cus, int workers)
+extern "C" double microseconds(int plain, const int32_t *len, int n, int hkv, int cus, int workers, int bytes)
 {
     std::vector<int32_t> first(n + 1);
     std::vector<uint32_t> split(n);
@@ -95,7 +104,7 @@ extern "C" double microseconds(int plain, const int32_t *len, int n, int hkv, in
     for (int r = 0; r < 20; ++r) {
         const auto t0 = std::chrono::steady_clock::now();
         for (int i = 0; i < 100; ++i)
-            plan(plain, len, n, hkv, cus, workers, first.data(), split.data());
+            plan(plain, len, n, hkv, cus, workers, bytes, first.data(), split.data());
         best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 100);
     }
     return best;
@@ -116,12 +125,12 @@ def lib(tmp_path_factory):
     return lib
 
 
-def _plan(lib, lens, hkv, workers, cus=CUS, plain=False):
+def _plan(lib, lens, hkv, workers, cus=CUS, plain=False, tile=8192):
     """(workgroups, first, split) of a step, or None for two launches."""
     lens = np.ascontiguousarray(lens, np.int32)
     first, split = np.full(len(lens) + 1, -1, np.int32), np.zeros(len(lens), np.uint32)
     p = [a.ctypes.data_as(ctypes.c_void_p) for a in (lens, first, split)]
-    blocks = lib.plan(int(plain), p[0], len(lens), hkv, cus, workers, p[1], p[2])
+    blocks = lib.plan(int(plain), p[0], len(lens), hkv, cus, workers, tile, p[1], p[2])
     return (blocks, first.tolist(), split.tolist()) if blocks else None
 
 
@@ -137,7 +146,8 @@ def test_plan_is_the_rule(lib, seed):
         if rng.random() < .5:
             lens[rng.integers(0, n)] = int(rng.integers(1, 500000))
         workers = int(rng.choice([768, 1024, 1, 100, 4096]))
-        got, want = (_plan(lib, lens, hkv, workers, cus, plain) for plain in (False, True))
+        tile = int(rng.choice([2048, 4096, 8192]))
+        got, want = (_plan(lib, lens, hkv, workers, cus, plain, tile) for plain in (False, True))
         assert got == want, (hkv, cus, workers, lens.tolist())
         one += got is not None
     assert one > 100
@@ -163,6 +173,11 @@ def test_plan_covers_every_unit(lib):
             assert per * 8 * k + rem == -(-int(L) // 16)
 
 
+@pytest.mark.parametrize("lens,hkv", [([2**31 - 16], 1), ([2**28, 2**27], 4)])
+def test_shares_past_the_quotients_field_take_two_launches(lib, lens, hkv):
+    assert _plan(lib, lens, hkv, 1) is None and _plan(lib, lens, hkv, 1, plain=True) is None
+
+
 def test_one_long_sequence_among_many_short_ones_takes_one_launch(lib):
     """Also where the units, a workgroup each, fill the chip: two launches were slower."""
     for lens, hkv in (([32000] + [200] * 127, 2), ([16000] + [100] * 63, 4)):
@@ -175,5 +190,5 @@ def test_plan_of_one_long_sequence_among_many_costs_little(lib):
     """Trying share after share costs many times the plan's passes."""
     lens = np.array([32000] + [200] * 127, np.int32)
     p = lens.ctypes.data_as(ctypes.c_void_p)
-    ours, plain = (lib.microseconds(v, p, len(lens), 2, CUS, 768) for v in (0, 1))
+    ours, plain = (lib.microseconds(v, p, len(lens), 2, CUS, 768, 8192) for v in (0, 1))
     assert ours < plain / 5, (ours, plain)
