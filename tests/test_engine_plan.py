@@ -10,6 +10,14 @@ import pytest
 from paper_2504_15930_amd import build
 
 CUS = 256   # of an MI355X, and four (three for bf16 with head_dim 128) workers per CU
+# Steps of the GPU tests of merged units: pages per sequence, KV heads, workgroups of the longest unit.
+# One workgroup writes the rows; up to eight pieces are merged in one batch of loads, more in batches
+# of eight; and more workgroups than CUs.
+MERGED = {"one": ([1, 8, 3], 2, 1), "seven": ([200], 2, 7), "eight": ([300], 1, 8), "nine": ([1152] * 3, 9, 9),
+          "sixteen": ([512] * 2, 8, 16), "seventeen": ([544] * 2, 7, 17), "thirty-two": ([768], 1, 32),
+          "past the chip": ([500] + [12] * 127, 2, 31)}
+LONG_PROMPT = 11000   # tokens of the long sample among short ones, in more than eight workgroups
+
 SOURCE = r"""
 #include <chrono>
 #include <vector>
@@ -171,6 +179,21 @@ def test_plan_covers_every_unit(lib):
             k, rem, per = (split[e] & 63) + 1, split[e] >> 6 & 1023, split[e] >> 16
             assert first[e + 1] - first[e] == 4 * k and k <= 32 and rem < 8 * k
             assert per * 8 * k + rem == -(-int(L) // 16)
+
+
+@pytest.mark.parametrize("workers,tile", [(768, 8192), (1024, 2048)])
+@pytest.mark.parametrize("name", MERGED)
+def test_batches_that_reach_every_merge(lib, name, workers, tile):
+    pages, hkv, groups = MERGED[name]
+    blocks, _, split = _plan(lib, [16 * n - 4 for n in pages], hkv, workers, tile=tile)
+    assert max((s & 63) + 1 for s in split) == groups
+    assert (blocks > CUS) == (name == "past the chip")
+
+
+@pytest.mark.parametrize("workers,hkv", [(768, 2), (1024, 2), (1024, 1)])
+def test_a_long_prompt_among_short_ones_is_merged_in_batches(lib, workers, hkv):
+    _, _, split = _plan(lib, [LONG_PROMPT + 1] + [300] * 15, hkv, workers)
+    assert (split[0] & 63) + 1 > 16
 
 
 @pytest.mark.parametrize("lens,hkv", [([2**31 - 16], 1), ([2**28, 2**27], 4)])

@@ -14,6 +14,7 @@ import oracle
 import parity
 from oracle import schedule as S
 from paper_2504_15930_amd import engine as E
+from test_engine_plan import LONG_PROMPT, MERGED
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -148,7 +149,7 @@ def test_engine_one_launch_every_step_matches_two_launch(kv, Hq, Hkv, D, queries
     rng = np.random.default_rng(33)
     M, BS = 60, 16
     prompt = rng.choice(np.array([0, 16, 32, 5, 47, 100, 260], np.int32), M)
-    prompt[7] = 3000
+    prompt[7] = LONG_PROMPT
     out = np.clip(np.exp(rng.normal(np.log(12), 0.9, M)), 1, 60).astype(np.int32)
     ref = S.simulate(prompt, out, out, BS, BS * int(((prompt + out + 15) // 16).max()),
                      int(((prompt + out + 15) // 16).max()), "lpt")
@@ -351,6 +352,31 @@ def test_engine_units_in_one_some_and_many_workgroups(kv, Hq, Hkv, D, pages):
     a, b = got[False], got[True]
     ulp = torch.exp2(torch.floor(torch.log2(torch.maximum(a.abs(), b.abs()).clamp_min(2.0 ** -126))) - 7)
     assert torch.isfinite(a).all() and ((a - b).abs() <= 2 * ulp + 2.0 ** -7 * vmax).all()
+
+
+@pytest.mark.parametrize("name", MERGED)
+@pytest.mark.parametrize("kv,D", [("bf16", 128), ("e4m3", 64)])
+def test_engine_every_merge_of_a_units_workgroups(kv, D, name):
+    """Units of 1 to 32 workgroups (the host's plan of these steps is checked on the CPU), with zero
+    queries: every row is the mean of its value rows, and the two launch modes differ in the last place
+    of the bf16 output at most, where a lost piece, or one tile of it, would move the mean by more."""
+    pages, Hkv, _ = MERGED[name]
+    prompt = np.array([16 * n - 5 for n in pages], np.int32)
+    out = np.full(len(pages), 8, np.int32)
+    got = {}
+    for two in (False, True):
+        print("merge of workgroups", kv, name, two, flush=True)
+        eng = E.Engine(prompt, out, out, batch_slots=len(pages), num_q_heads=3 * Hkv, num_kv_heads=Hkv, head_dim=D,
+                       kv_fp8=kv == "e4m3", seed=4, two_launch=two, history_steps=8)
+        eng.q.zero_()
+        assert eng.run() == 8
+        torch.cuda.synchronize()
+        got[two] = eng.history.float().cpu()
+        eng.close()
+    a, b = got[False], got[True]
+    assert torch.isfinite(a).all() and torch.isfinite(b).all()
+    ulp = torch.exp2(torch.floor(torch.log2(torch.maximum(a.abs(), b.abs()).clamp_min(2.0 ** -126))) - 7)
+    assert not ((a - b).abs() > ulp + 1e-5).any(), f"max |diff| {float((a - b).abs().max()):.3g}"
 
 
 @pytest.mark.parametrize("kv,BS,Hkv", [("e4m3", 300, 8), ("e4m3", 256, 8), ("bf16", 300, 8)])
