@@ -75,7 +75,8 @@ typedef enum sl_status {
  *   seq_lens        [batch]                                        int32
  * Supported: head_dim 64 or 128; page_size 16; 1 <= num_q_heads /
  * num_kv_heads <= 16; batch <= 8192; batch * max_blocks_per_seq *
- * num_kv_heads < 2^31.
+ * num_kv_heads < 2^28; batch * num_q_heads < 2^24; num_pages * num_kv_heads
+ * and 16 * max_blocks_per_seq < 2^31.
  */
 typedef struct sl_attn_desc {
     int32_t batch;              /* sequences in the step; 0 makes every call a no-op */
@@ -86,9 +87,9 @@ typedef struct sl_attn_desc {
     int32_t max_blocks_per_seq; /* row length of block_table */
     int32_t num_pages;          /* pages in each pool; valid page ids are [0, num_pages) */
     int32_t num_workers;        /* split-KV workers (wavefronts). 0: library default
-                                   (three per CU for bf16 with head_dim 128, else four
-                                   per CU); 1..65536: exactly this
-                                   many. The result does not depend on it beyond fp32
+                                   (three per CU for a bf16 cache with head_dim 128, else,
+                                   and for prefix-shared attention, four per CU);
+                                   1..65536: exactly this many. The result does not depend on it beyond fp32
                                    rounding; tests vary it to exercise the merge. */
     hipStream_t stream;         /* stream the work is enqueued on (0: null stream) */
     void *workspace;            /* device scratch, >= sl_decode_attn_workspace_size bytes,

@@ -110,9 +110,9 @@ sl_status check_desc(const sl_attn_desc *d)
         return SL_ERR_UNSUPPORTED;
     if (d->batch > kMaxBatch)
         return SL_ERR_UNSUPPORTED;
-    // Tile-list entries: at most 2^28 tiles (8-byte entries addressed with
-    // 32-bit byte offsets), page-head tile indices and query-row numbers that
-    // fit their fields.
+    // What the kernels' fields and 32-bit offsets hold: 2^28 block-table
+    // entries times KV heads (a stream's tiles), token positions, page-head
+    // tile indices, and units and query rows of 24 bits.
     if ((long long)d->batch * d->max_blocks_per_seq * d->num_kv_heads >= (1LL << 28) ||
         (long long)d->max_blocks_per_seq * kPageSize >= (1LL << 31) ||
         (long long)d->num_pages * d->num_kv_heads >= (1LL << 31) ||
@@ -138,8 +138,8 @@ sl_status resolve_workers(const sl_attn_desc *d, bool fp8, int *nw, bool prefix 
     // workgroups per four CUs (1.5-2.5% faster than one per CU, as fewer
     // streams compete for the memory; 640 or fewer workers, or 1280 and more,
     // were slower). With head_dim 64 a bf16 tile carries half the bytes, and
-    // one per CU is as fast or faster (132 against 130 us on 384 sequences of
-    // 1..2048 tokens; one tile per step: 150 against 132). Two waves per SIMD
+    // one per CU is as fast or faster (384 sequences of 1..2048 tokens: 130 us,
+    // with three per four CUs 132; with one tile per step 132 and 150). Two waves per SIMD
     // were slower for all but E4M3 with head_dim 64 and one tile per step.
     // Prefix-shared attention keeps one own-page workgroup per CU beside its shared-page
     // workgroups (three per four CUs was 12% slower).

@@ -40,8 +40,6 @@ namespace {
 
 typedef short i16x2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
-
 // One E4M3 code -> binary32, exact (the bf16 conversion covers every code).
 __device__ __forceinline__ float e4m3_to_f32(uint32_t code)
 {

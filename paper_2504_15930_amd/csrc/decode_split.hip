@@ -7,7 +7,7 @@ namespace sl {
 namespace {
 
 // Every workgroup derives the tile stream from the lengths and the block
-// table (its dynamic LDS holds the page prefix sum and the lengths).
+// table (its dynamic LDS holds the prefix sum of steps and the lengths).
 //
 // Worker w = wave * gridDim.x + block: the four wavefronts of a workgroup take
 // ranges a quarter of the stream apart, so a CU streams four unrelated

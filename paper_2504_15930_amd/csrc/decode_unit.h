@@ -80,8 +80,6 @@ constexpr int step_tiles() { return D == 64 ? (FP8 ? 4 : 2) : (FP8 ? 2 : 1); }
 constexpr int kPipelineDepth = 2;
 constexpr int kRawBufferWord3 = 0x00020000;  // untyped 32-bit buffer resource (CDNA3/4)
 
-__device__ __forceinline__ u32x4_t ld128(const uint8_t *p) { return *reinterpret_cast<const u32x4_t *>(p); }
-
 // Two fp32 -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {

@@ -17,10 +17,10 @@
 // once the kernels that read it have completed, lets the host run ahead of
 // the GPU.
 //
-// A bf16 step whose attention fits the chip in one pass of workgroups runs
-// in a single launch instead (engine_unit_step_kernel): the host passes the
-// step's sequences and lengths as kernel arguments, gives each (sequence, KV
-// head) unit a share of the CUs in whole workgroups, and the unit's
+// A step with little attention work runs in a single launch instead
+// (engine_unit_step_kernel): the host passes the step's sequences and lengths
+// as kernel arguments, gives each (sequence, KV head) unit so many workgroups
+// that the waves' shares are about equal (unit_plan.h), and the unit's
 // workgroups combine their states themselves; the next step's append rides
 // in the same launch unless it would reuse a page freed in this step, which
 // this step's attention may still be reading. Empty slots' rows are cleared

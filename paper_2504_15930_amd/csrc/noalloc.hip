@@ -1,7 +1,7 @@
 // sl_decode_attn_noalloc: decode attention with a bf16 cache for callers that
 // cannot allocate device memory (code under HIP graph capture, tight serving
 // loops, harnesses that forbid hipMalloc). It runs exactly the kernels of
-// sl_decode_attn; their scratch (the page prefix sum and the split-KV partial
+// sl_decode_attn; their scratch (the prefix sum of steps and the split-KV partial
 // states) lives in a fixed array of this library instead of a caller
 // workspace.
 //

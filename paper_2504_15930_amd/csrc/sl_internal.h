@@ -5,21 +5,25 @@
 //
 // Work decomposition. A "unit" is one (sequence b, KV head g) pair and owns
 // n_b = ceil(L_b / 16) page-head tiles (16 tokens x head_dim of one KV head).
-// Units are laid out b-major, g-minor, and their tiles are numbered
-// consecutively, giving W = Hkv * sum_b n_b tiles in total. Worker w (one
-// wavefront) owns tiles [floor(w W / NW), floor((w + 1) W / NW)): every worker
-// reads the same number of tiles (+-1) whatever the length skew, so a few very
-// long sequences are spread over many workers instead of leaving most of the
-// chip idle (the on-chip analogue of StreamRL's skewness bubbles, Section 2.4
-// and Section 5.1).
+// A step is NT = 1, 2 or 4 consecutive tiles of a unit (step_tiles in
+// decode_unit.h; fewer at the unit's end). Units are laid out b-major, g-minor,
+// and their steps are numbered consecutively, giving W = Hkv * sum_b
+// ceil(n_b / NT) steps in total. Worker w (one wavefront) owns steps
+// [floor(w W / NW), floor((w + 1) W / NW)): every worker takes the same number
+// of steps (+-1) whatever the length skew, so a few very long sequences are
+// spread over many workers instead of leaving most of the chip idle (the
+// on-chip analogue of StreamRL's skewness bubbles, Section 2.4 and Section
+// 5.1). In tiles the ranges are as equal as the units' last steps are full: a
+// range of sequences of one page has 1 / NT of the tiles of one in a long
+// sequence.
 //
-// A worker streams its range as one flat sequence of tiles, which every
+// A worker streams its range as one flat sequence of steps, which every
 // workgroup derives itself: it scans the lengths (and, with prefix sharing,
-// the group descriptions) into LDS, locates its workers' first tiles by
-// binary search and walks the block table with a cursor. There is no
-// partitioning launch and no tile list in memory. The block-table entry of a
-// tile is fetched a pipeline turn ahead, so unit boundaries inside the range
-// cost no dependent load and do not drain the load pipeline.
+// the group descriptions) into LDS, and every wavefront works out its range 64
+// steps at a time, one per lane: the unit by binary search, the pages, and
+// their block-table entries, loaded while the 64 steps before stream. There is
+// no partitioning launch and no list of steps in memory, and unit boundaries
+// inside the range cost no dependent load and do not drain the load pipeline.
 //
 // (For the shared pages of prefix-shared attention a worker is a workgroup
 // whose four wavefronts stream the same range, one query block each.)
@@ -43,7 +47,7 @@ constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;          // split kernel: 4 independent workers per block
 constexpr int kMaxGroup = 16;              // query heads per KV head (one MFMA column block)
 constexpr int kMaxBatch = 8192;            // the split kernel keeps two ints per sequence in LDS
-constexpr int kMergeThreads = 256;         // one wave per unit, four units per block
+constexpr int kMergeThreads = 256;         // one wave per (sequence, query head)
 constexpr int kMaxWorkers = 1 << 16;       // keeps partial-state offsets below 2^31 bytes
 // A worker is given at least this many tiles: a small stream (a small batch, a
 // short context) is split over fewer workers rather than cut into pieces of
@@ -65,7 +69,8 @@ constexpr int kMinTilesWide = 8;
 
 // Workers that take part in a stream of `total` steps of step_tiles tiles (the
 // others exit at once); both the split kernel and the merge derive it from the
-// same total (below 2^28 tiles). `wide`: kMinTilesWide beyond this many workers.
+// same total. A unit's last step counts as a full one (below 2^30 tiles so
+// counted). `wide`: kMinTilesWide beyond this many workers.
 __host__ __device__ inline int effective_workers(long long total, int num_workers, int step_tiles, int wide)
 {
     const int tiles = (int)total * step_tiles;
@@ -124,7 +129,7 @@ constexpr int kPrefixRows = 16 * kPrefixBlocks;
 constexpr int kMetaUnitShift = 8;
 
 struct Workspace {
-    int32_t *cum_pages;   // [B + 1] exclusive prefix sum of pages per sequence (written by the split kernel)
+    int32_t *cum_pages;   // [B + 1] exclusive prefix sum of steps per sequence and KV head (written by the split kernel)
     float *part_ml;       // [2 NW][G][2]  (running max in log2 units, sum of weights)
     float *part_acc;      // [2 NW][G][D]  un-normalised weighted value sums
 };
@@ -148,7 +153,7 @@ struct SplitParams {
     float *unit_ml;
     float *unit_acc;
     // The kernel derives every tile from the lengths and the block table
-    // itself; workgroup 0 stores the page prefix sum in cum_out for the merge
+    // itself; workgroup 0 stores the prefix sum of steps in cum_out for the merge
     // (plain attention; prefix sharing stores its sums through PrefixParams).
     const int32_t *seq_lens;
     const int32_t *block_table;
@@ -263,12 +268,12 @@ size_t prefix_workspace_layout(void *base, int batch, int max_blocks, int num_kv
 size_t workspace_layout(void *base, int batch, int max_blocks, int num_kv_heads, int group,
                         int head_dim, int num_workers, Workspace *ws);
 
-// The split kernel's dynamic LDS: the page prefix sum (B + 1 ints) and the
+// The split kernel's dynamic LDS: the prefix sum of steps (B + 1 ints) and the
 // lengths (B ints).
 inline size_t split_dynamic_lds(int batch) { return sizeof(int32_t) * (2 * (size_t)batch + 1); }
-// The fused prefix kernel's: for the sequences the own-page prefix sum, the
-// shared pages and the lengths (3 B + 2 ints), for the sub-groups the
-// shared-page prefix sum and the packed first member and size (2 S + 1 ints).
+// The fused prefix kernel's: for the sequences the prefix sum of own steps, the
+// shared pages and the lengths (3 B + 2 ints), for the sub-groups the prefix
+// sum of shared steps and the packed first member and size (2 S + 1 ints).
 inline size_t prefix_dynamic_lds(int batch, int max_sub)
 {
     return sizeof(int32_t) * (3 * (size_t)batch + 2 * (size_t)max_sub + 3);

@@ -34,7 +34,7 @@ def test_step_and_chunk_edges(D, kv, workers):
 @pytest.mark.parametrize("pieces", [2, 8, 9, 16, 17, 33, 64, 65, 129])
 @pytest.mark.parametrize("D,kv", KINDS)
 def test_unit_cut_into_many_pieces(D, kv, pieces):
-    """One KV head over `pieces` workers (a worker takes at least eight tiles): the merge's first
+    """One KV head over `pieces` workers (a worker takes at least four tiles): the merge's first
     batch of rows, the loop after it and the second chunk of 64 weights."""
     L = [16 * 8 * pieces - 7]
     _say("pieces", D, kv, pieces)
