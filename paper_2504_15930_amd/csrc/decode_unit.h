@@ -246,10 +246,17 @@ __device__ __forceinline__ void issue_step(Step<D, FP8, NT> &st, const SplitPara
         // against 137 us; E4M3 D = 128, 313 against 316).
         if (NT > 1 || with_q)
             load_q<D, FP8>(st.q, p, row0, with_q, n, quad);
-    } else {   // rows past the shared unit's read its first row (never written out)
+    } else if (with_q) {
+        // Issued for a unit's first step only: four wavefronts load every tile
+        // here, from L2, and with two such workgroups on a CU the load
+        // instructions themselves are short. (With loads of zeros in the other
+        // steps, a third of them all: 130 prompts of 7030 tokens x 14 samples,
+        // 16/1 heads, bf16, D = 128 697 us instead of 619; 16 of 4000 x 24,
+        // 12/12 heads, D = 64 155 instead of 126.)
+        // Rows past the shared unit's read its first row (never written out).
         const int r = 16 * blk + n, G = p.group;
         const uint32_t rel = r < ((st.valid >> 8) + 1) * G ? (uint32_t)((r / G) * p.num_q_heads + r % G) : 0u;
-        const __amdgpu_buffer_rsrc_t qr = buffer_of(p.q + (size_t)row0 * D, with_q ? 0xffffffffu : 0u);
+        const __amdgpu_buffer_rsrc_t qr = buffer_of(p.q + (size_t)row0 * D, 0xffffffffu);
 #pragma unroll
         for (int s = 0; s < D / 32; ++s)
             st.q[s] = __builtin_bit_cast(
