@@ -86,8 +86,14 @@ __host__ __device__ inline int wide_from(int num_workers, bool fp8) { return fp8
 // Prefix sharing: shared-page workgroups that take part in a call. The launch
 // holds the own-page workgroups and up to twice `base` shared ones, and a CU
 // holds two such workgroups; own-page workgroups without work exit at once,
-// and a shared workgroup beyond `base` takes such an idle slot, so a batch with
-// few own pages still streams its shared pages with two workgroups per CU.
+// and shared workgroups beyond `base` take their slots, so that a batch with
+// few own pages still streams its shared pages with two workgroups per CU. All
+// ranges are equally long, and on a CU with two shared workgroups each takes
+// longer: with few such CUs their ranges end late, so beyond `base` there are
+// three quarters of it or none. Shared workgroups (base 256) and time, MI355X:
+//   130 prompts of 7030 tokens x 14 samples, 16/1 heads, D = 128   284 619 us, 256 493
+//   32 of 4000 x 16, 28/4 heads                                    382 169 us, 256 148
+//   32 of 4000 x 16, 16/1 heads                                    480  76 us, 256  83
 // The split kernel and the merge derive it from the same totals (own tiles).
 __host__ __device__ inline int effective_shared_workers(long long own_total, int own_workers, int base,
                                                         int max_workers, int step_tiles, bool fp8)
@@ -99,7 +105,7 @@ __host__ __device__ inline int effective_shared_workers(long long own_total, int
                   kWavesPerBlock
             : 0;
     const int idle = own_blocks - active;
-    const int n = base + (idle < base ? idle : base);
+    const int n = 4 * idle >= 3 * base ? base + (idle < base ? idle : base) : base;
     return n < max_workers ? n : max_workers;
 }
 constexpr size_t kAlign = 256;

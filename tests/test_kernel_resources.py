@@ -69,6 +69,8 @@ def sizes(tmp_path_factory):
         'extern "C" size_t split_bytes(int b) { return sl::split_dynamic_lds(b); }\n'
         'extern "C" size_t prefix_bytes(int b, int ng, int g)\n'
         '{ return sl::prefix_dynamic_lds(b, sl::prefix_max_sub(b, ng, g)); }\n'
+        'extern "C" int shared_workers(int own_tiles, int own_workers, int base, int most)\n'
+        '{ return sl::effective_shared_workers(own_tiles, own_workers, base, most, 1, false); }\n'
         'extern "C" int max_batch(int prefix) { return prefix ? sl::kMaxPrefixBatch : sl::kMaxBatch; }\n')
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     out = str(d / "sizes.so")
@@ -113,6 +115,20 @@ def test_two_prefix_workgroups_per_cu(static_lds, sizes, D, kv, batch, groups, g
     """The shared pages stream beside the own ones: two workgroups on a CU."""
     one = _kernel(static_lds, "prefix_split_kernel", D, kv) + sizes.prefix_bytes(batch, groups, group)
     assert 2 * one <= LDS_PER_CU
+
+
+@pytest.mark.parametrize("own,base,most", [(1024, 256, 512), (1216, 304, 608), (64, 16, 32), (4, 1, 2), (9, 2, 4), (1, 1, 1)])
+def test_shared_workgroups_of_a_launch(sizes, own, base, most):
+    """Prefix sharing adds as many workgroups to the shared pages' as own ones are idle, if that gives most of the
+    CUs two; a few more than one per CU would all end late. Never more than own and shared slots together."""
+    slots, seen = (own + 3) // 4 + base, set()
+    for tiles in range(0, 8 * own + 2):
+        n = sizes.shared_workers(tiles, own, base, most)
+        busy = (min(own, max(1, -(-tiles // 4))) + 3) // 4 if tiles else 0
+        assert base <= n <= most and n + busy <= slots
+        assert n == base or 4 * (n - base) >= 3 * base or n == most
+        seen.add(n)
+    assert base in seen and most in seen
 
 
 @pytest.mark.parametrize("D", [64, 128])
