@@ -281,8 +281,8 @@ __device__ __forceinline__ void issue_step(Step<D, FP8, NT> &st, const SplitPara
 // 186 us instead of 155; 256 sequences of 1..2048 tokens with 4096 workers 74
 // instead of 65. With 4096 sequences in more than 3862 groups the prefix kernel no
 // longer fitted a CU at all.)
-template <int D, bool FP8, int NT>
-__device__ __forceinline__ void regroup_k(const Tile<D, FP8> (&t)[NT], uint8_t *lds, int lane, int n, int quad,
+template <int D, bool FP8, int NT, int N>
+__device__ __forceinline__ void regroup_k(const Tile<D, FP8> (&t)[N], uint8_t *lds, int lane, int n, int quad,
                                           u32x4_t (&kc)[NT][FP8 ? D / 64 : D / 32])
 {
     constexpr int R = D * (FP8 ? 1 : 2);   // bytes per row
@@ -340,8 +340,8 @@ __device__ __forceinline__ void reset(Piece<D> &st)
     st.l = 0.f;
 }
 
-// One step of the online softmax over NT tiles. `valid` = live tokens of the
-// step (1 .. 16 NT; the first tile has at least one).
+// One step of the online softmax over the first NT of its tiles. `valid` = live
+// tokens of the step (1 .. 16 NT; the first tile has at least one).
 //
 // With several tiles the score products are independent chains, the running
 // maximum is looked at once for all of them, and the value product takes two
@@ -349,8 +349,8 @@ __device__ __forceinline__ void reset(Piece<D> &st)
 // stands for token 4 quad + (i & 3) of tile i / 4 in both operands, so the
 // weights enter exactly as the score MFMAs left them, as with one tile and
 // v_mfma_f32_16x16x16bf16_1k.
-template <int D, bool FP8, int NT>
-__device__ __forceinline__ void compute_step(Piece<D> &st, const Tile<D, FP8> (&t)[NT],
+template <int D, bool FP8, int NT, int N>
+__device__ __forceinline__ void compute_step(Piece<D> &st, const Tile<D, FP8> (&t)[N],
                                              const bf16x8_t (&qop)[D / 32], float score_mul, int valid, uint8_t *lds,
                                              int lane, int n, int quad)
 {
@@ -1028,8 +1028,23 @@ __device__ __forceinline__ void split_unit_worker(const SplitParams &p, int w, c
                 }
                 started |= (meta & kMetaFirst) != 0;
                 bad |= (meta & kMetaBad) != 0;
-                compute_step<D, FP8, NT>(st, t.t, qop, p.scale_log2, kShared ? t.valid & 0xff : t.valid, lds, lane, n,
-                                         quad);
+                // Of a step of four tiles a short unit has one or two, and the others would
+                // cost as much; only a unit's last step can lack any. E4M3, D = 64, MI355X,
+                // four tiles -> those that there are: 5663 sequences of one page, 3/3
+                // heads, 45.5 -> 37.0 us (steps of one tile 36.4); 8192, 8/2 heads,
+                // 62.0 -> 54.3; of 3 or 4 pages 32.6 -> 33.7 (38.4 to 42.6); longer ones the
+                // same. (With the choice in every step those took 1% longer. Shared units
+                // are long: their loop lost 5%.)
+                constexpr bool kFew = NT == 4 && !kShared;
+                const int valid = kShared ? t.valid & 0xff : t.valid;
+                if (kFew && (meta & kMetaLast) == 0)
+                    compute_step<D, FP8, NT>(st, t.t, qop, p.scale_log2, kPageSize * NT, lds, lane, n, quad);
+                else if (kFew && valid <= kPageSize)
+                    compute_step<D, FP8, 1>(st, t.t, qop, p.scale_log2, valid, lds, lane, n, quad);
+                else if (kFew && valid <= 2 * kPageSize)
+                    compute_step<D, FP8, 2>(st, t.t, qop, p.scale_log2, valid, lds, lane, n, quad);
+                else
+                    compute_step<D, FP8, NT>(st, t.t, qop, p.scale_log2, valid, lds, lane, n, quad);
                 if (kShared && ((meta & kMetaLast) != 0 || ends)) {
                     // A shared unit's state is always merged: a whole one goes to the unit area
                     // (indexed by first query row / G), a cut one to the worker's slot; block blk
