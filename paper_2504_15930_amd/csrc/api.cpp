@@ -361,7 +361,8 @@ sl_status run_prefix(const sl_attn_desc *d, const uint16_t *q, const void *k_pag
     sp_.max_blocks = d->max_blocks_per_seq;
     sp_.num_pages = d->num_pages;
     // Shared-page pass: one workgroup of four wavefronts per worker; up to
-    // twice the base count when own-page workgroups are idle.
+    // twice the base count where most own-page workgroups are idle
+    // (effective_shared_workers).
     const int nws = shared_workers(nw);
     const int nws_max = nw > 2 * nws ? 2 * nws : (nw > nws ? nw : nws);   // slots are sized for nw workers
     SplitParams shp = sp_;
